@@ -19,7 +19,6 @@ namespace mlp {
 constexpr int IN = 96, HID = 64, OUT = 3, OUT_PAD = 16, NFEAT = 87;
 constexpr int XS = 104;  // LDS row stride (bf16) of a 96-wide tile: 16-byte rows, no bank conflicts
 constexpr int HS = 72;   // LDS row stride (bf16) of a 64-wide tile
-constexpr int YS = 40;   // LDS row stride (bf16) of the output-gradient tile (K padded to 32)
 
 // Packed fp32 parameter vector: W1 [64][96], b1 [64], W2 [64][64], b2 [64], W3 [3][64], b3 [3].
 constexpr int OFF_W1 = 0;
@@ -32,6 +31,7 @@ constexpr int NPARAM = OFF_B3 + OUT;  // 10563
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Network as the edge kernel reads it (device memory).  Weights in BF16,
@@ -60,18 +60,36 @@ __device__ inline bf16x8 frag_k1(const bf16* base, int ld, int mn0, int k0) {
   return *reinterpret_cast<const bf16x8*>(base + (mn0 + (l & 15)) * ld + k0 + 8 * (l >> 4));
 }
 
-// Fragment with the k-elements `ldk` apart and rows/columns `ld` apart.
-__device__ inline bf16x8 frag_gather(const bf16* base, int ld, int ldk, int mn0, int k0) {
-  const int l = lane();
-  const bf16* p = base + (mn0 + (l & 15)) * ld + (k0 + 8 * (l >> 4)) * ldk;
-  bf16x8 v;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = p[j * ldk];
-  return v;
-}
-
 __device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// bf16(tanhf(z)), bit for bit, at about half tanhf's cost.  tanh is first
+// formed as 1 - 2 e / (1 + e), e = exp(-2 |z|) from the hardware exponential
+// and reciprocal, and below 0.3, where that would cancel, as its Taylor
+// polynomial to z^9: at most TANH_ULP ulps from tanhf for every float (checked
+// one by one).  Where one of the four values lies that close to a tie of the
+// rounding to BF16, tanhf decides (about 1 wavefront in 30).
+constexpr int TANH_ULP = 4;
+__device__ inline bf16x4 tanh_bf16(f32x4 z) {
+  f32x4 t;
+  uint32_t near = 0xffffu;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float x = z[i], a = fabsf(x), x2 = x * x;
+    const float e = __builtin_amdgcn_exp2f(-2.8853900817779268f * a);  // 2 / ln 2
+    const float far = copysignf(fmaf(-2.f * e, __builtin_amdgcn_rcpf(1.f + e), 1.f), x);
+    float p = fmaf(x2, 62.f / 2835.f, -17.f / 315.f);
+    p = fmaf(x2, p, 2.f / 15.f);
+    p = fmaf(x2, p, -1.f / 3.f);
+    t[i] = a < 0.3f ? fmaf(x * x2, p, x) : far;
+    near = min(near, (__float_as_uint(t[i]) + (0x8000u + TANH_ULP)) & 0xffffu);
+  }
+  if (__builtin_expect(near <= 2 * TANH_ULP, 0)) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) t[i] = tanhf(z[i]);
+  }
+  return bf16x4{(bf16)t[0], (bf16)t[1], (bf16)t[2], (bf16)t[3]};
 }
 
 // One dense layer for the 16 rows of this wavefront:
