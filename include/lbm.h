@@ -139,7 +139,12 @@ int lbm_set_farfield(lbm_ctx* ctx, double beta, double rho_ref, double ux_ref, d
 int lbm_set_velocity_edge(lbm_ctx* ctx, double ux, double uy);
 
 /* Advance n >= 0 time steps (stream, NSBC, collide; eqs. lbe_0, nes_0..nes_4,
- * lbe_1).  Asynchronous; the context's time advances by n.  The call is a
+ * lbe_1).  Asynchronous; the context's time advances by n.  Until a launch
+ * shape is chosen (lbm_set_tile, lbm_autotune, lbm_set_two_step or
+ * lbm_autotune_two_step) and while fusion is on, overlap, per-kernel timing
+ * and the closure off, the library picks the launches of n >= 2 steps by the
+ * lattice's size, edges and storage: several steps per launch, with the
+ * results of single steps, bit for bit.  The call is a
  * roctx range named "lbm_step" (as are the other stepping and tuning calls,
  * each under its own name), visible to rocprofv3 --marker-trace. */
 int lbm_step(lbm_ctx* ctx, int32_t n);
@@ -319,8 +324,8 @@ int lbm_set_fused(lbm_ctx* ctx, int on);
  * lattice shapes (lbm_ens_set_two_step refuses them).
  * lbm_two_step_count / lbm_two_step_describe ("2step:..." or "3step:...")
  * list the candidate shapes and lbm_two_step_steps gives a shape's steps per
- * launch; lbm_set_two_step selects one (-1 turns the sweeps off, the
- * default) and fails for lattices it does not support.  With a shape
+ * launch; lbm_set_two_step selects one (-1: single-step launches; lbm_get_two_step
+ * also reports -1 while none is selected) and fails for lattices it does not support.  With a shape
  * selected, lbm_step advances groups of that many steps with it; after
  * three-step launches a remainder of two steps takes one two-step launch
  * (the best two-step shape lbm_autotune_two_step timed, else a default per

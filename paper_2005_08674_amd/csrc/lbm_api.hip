@@ -308,7 +308,7 @@ struct lbm_ctx {
   std::vector<char> ev_two;  // per 4-event group: 1 = a two-step launch (events 0, 1)
   double two_ms = 0;
   int64_t two_n = 0;
-  // multi-step sweep shape (-1: off)
+  // multi-step sweep shape (-1: off, or the library's choice until `chosen`)
   int two_step = -1;
   // a closure launch's wait of the stream for its edge-tile kernel (on the
   // second stream) deferred to the next launch or to the end of lbm_step
@@ -319,6 +319,8 @@ struct lbm_ctx {
   int rem_best[5] = {-1, -1, -1, -1, -1};
   // edge segments and bulk tiles of a step in one launch
   bool fused = true;
+  // a launch shape has been chosen (lbm_set_tile, lbm_set_two_step or a tuner)
+  bool chosen = false;
 };
 
 namespace {
@@ -470,6 +472,15 @@ void multi_name(int id, char* buf, size_t len) {
     lbm::three_step_name(id - lbm::num_two_step(), buf, len);
 }
 
+int multi_named(const char* want) {
+  char buf[64];
+  for (int id = 0; id < multi_count(); ++id) {
+    multi_name(id, buf, sizeof(buf));
+    if (std::strcmp(buf, want) == 0) return id;
+  }
+  return -1;
+}
+
 // Two or three steps in one launch of multi-step shape `id` (same results as
 // that many step_once calls).
 int step_multi(lbm_ctx* c, int id) {
@@ -508,17 +519,62 @@ int rem_shape(const lbm_ctx* c, int k) {
     const char* want = c->p.store == LBM_STORE_F64   ? "2step:64x12/512+xcdband+nts"
                        : c->p.store == LBM_STORE_F32 ? "2step:64x20/768+xcdband+nts"
                                                      : "2step:64x8/512+march7xh96+xcdband+nts";
-    char buf[64];
-    for (int id = 0; id < lbm::num_two_step(); ++id) {
-      lbm::two_step_name(id, buf, sizeof(buf));
-      if (std::strcmp(buf, want) == 0 && multi_supported(c->L, id)) return id;
-    }
+    const int id = multi_named(want);
+    if (multi_supported(c->L, id)) return id;
   }
   return -1;
 }
 
-bool use_two_step(const lbm_ctx* c) {
-  return c->two_step >= 0 && !c->overlap && multi_supported(c->L, c->two_step);
+// Whether lbm_step chooses its launches by itself: nobody has chosen one, and
+// nothing asks for the single-step kernels (timing counts their launches).
+bool free_choice(const lbm_ctx* c) { return !c->chosen && !c->timing && use_fused(c); }
+
+// Multi-step shape of a free lattice with four NSBC edges, -1 for the deep
+// sweep.  The 64-wide sweeps recompute less margin per step than the deep one
+// but take few blocks: measured, us per step in runs of 60 (three-step tiles /
+// march / best deep shape), they win from 2048^2 on in FP64 (50 / 46 / 60) and
+// FP32 (25 / 24 / 33) and trail or tie below (1024 x 1024: 14.9 / 15.8 / 14.4
+// and 8.3 / 9.2 / 8.7; in runs of 10, where three steps leave a remainder, the
+// deep sweep is ahead throughout); the 16-bit formats, whose deep sweep pays
+// for its conversions, change at 512^2 (3.7 / 6.2 / 3.9; 701^2: 4.4 / 6.5 / 5.7).
+int free_multi(const lbm_ctx* c) {
+  const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
+  const bool half = c->lay.esize == 2;
+  if (nodes < (half ? (int64_t)1 << 18 : (int64_t)1 << 21)) return -1;
+  const int id = multi_named(nodes < (int64_t)1 << 21 ? "3step:64x12/768+xcdband+nts"
+                                                      : "3step:64x12/768+march11xh96+xcdband+nts");
+  return multi_supported(c->L, id) ? id : -1;
+}
+
+// Deep-sweep shape of a free lattice: the smallest tile that leaves every
+// block a CU of its own, so that a level costs latency only (128^2 FP64: 2.1 us
+// a step with 8 x 8 tiles, 2.5 with 16 x 16; 256^2: 5.2 and 2.6); a larger
+// lattice takes the widest, which recomputes the least margin.  -1 if the
+// lattice is too small for it.
+int deep_shape(const lbm_ctx* c) {
+  int id = 0;
+  for (; id < lbm::num_deep() - 1 && lbm::deep_tiles(c->L, id) > 256; ++id) {
+  }
+  while (id >= 0 && !lbm::deep_supported(c->L, id)) --id;
+  return id;
+}
+
+// n steps in as few deep launches as they take, of nearly equal length.
+int step_deep(lbm_ctx* c, int id, int n) {
+  for (int m = (n + lbm::deep_steps(id) - 1) / lbm::deep_steps(id); m > 0; --m) {
+    const int k = (n + m - 1) / m;
+    HIPCHK(lbm::launch_deep(c->L, c->parity, id, k, c->stream));
+    c->parity ^= 1;
+    c->t += k;
+    n -= k;
+  }
+  return LBM_OK;
+}
+
+// The multi-step shape lbm_step takes, -1 for none.
+int use_multi(const lbm_ctx* c) {
+  const int id = free_choice(c) ? free_multi(c) : c->two_step;
+  return id >= 0 && !c->overlap && multi_supported(c->L, id) ? id : -1;
 }
 
 }  // namespace
@@ -649,10 +705,10 @@ int lbm_step(lbm_ctx* c, int32_t n) {
     HIPCHK(hipEventRecord(c->ev_edge, c->stream));
   }
   int32_t s = 0;
-  if (use_two_step(c)) {
-    const int k = multi_steps(c->two_step);
+  if (const int id = use_multi(c); id >= 0) {
+    const int k = multi_steps(id);
     int rc = LBM_OK;
-    for (; s + k <= n && rc == LBM_OK; s += k) rc = step_multi(c, c->two_step);
+    for (; s + k <= n && rc == LBM_OK; s += k) rc = step_multi(c, id);
     // a remainder of two or more steps: one launch of a shape with that
     // many steps instead of single steps (same results)
     if (rc == LBM_OK && n - s >= 2) {
@@ -666,6 +722,12 @@ int lbm_step(lbm_ctx* c, int32_t n) {
     const hipError_t e = settle_join(c, c->join_pending);
     if (rc) return rc;
     HIPCHK(e);
+  } else if (n >= 2 && free_choice(c)) {
+    const int id = deep_shape(c);
+    if (id >= 0) {
+      if (int rc = step_deep(c, id, n)) return rc;
+      s = n;
+    }
   }
   for (; s < n; ++s) {
     int rc = step_once(c);
@@ -798,6 +860,7 @@ int lbm_set_tile(lbm_ctx* c, int32_t id) {
   if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
   if (id < 0 || id >= lbm::num_tiles()) return fail(LBM_ERR_ARG, "tile id %d out of range", id);
   c->tile = id;
+  c->chosen = true;
   return LBM_OK;
 }
 
@@ -895,6 +958,7 @@ int lbm_autotune(lbm_ctx* c, int32_t reps, int32_t* best, float* times_ms) {
   if (rc) return rc;
   if (int r = snap.restore()) return r;
   c->tile = best_id;
+  c->chosen = true;
   *best = best_id;
   return LBM_OK;
 }
@@ -940,6 +1004,7 @@ int lbm_set_two_step(lbm_ctx* c, int32_t id) {
                 "their LDS for this format",
                 id);
   c->two_step = id;
+  c->chosen = true;
   return LBM_OK;
 }
 
@@ -1015,6 +1080,7 @@ int lbm_autotune_two_step(lbm_ctx* c, int32_t reps, int32_t* best, float* times_
   if (rc) return rc;
   if (int r = snap.restore()) return r;
   c->two_step = best_id;
+  c->chosen = true;
   for (int k = 2; k <= 4; ++k)
     if (best_k[k] >= 0) c->rem_best[k] = best_k[k];
   *best = best_id;

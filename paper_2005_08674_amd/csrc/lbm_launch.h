@@ -43,6 +43,13 @@ hipError_t launch_three_step(const LatDesc& L, int parity, int id, hipStream_t s
                              hipEvent_t fork = nullptr, hipEvent_t join = nullptr, int flags = 0);
 int three_step_tile_rows(int id);
 int three_step_min_rows();
+// deep sweep (lbm_deep.hip): k steps (1 <= k <= deep_steps(id)) in one launch
+// on a lattice with any edges, without the learned closure
+int num_deep();
+int deep_steps(int id);
+int64_t deep_tiles(const LatDesc& L, int id);
+bool deep_supported(const LatDesc& L, int id);
+hipError_t launch_deep(const LatDesc& L, int parity, int id, int k, hipStream_t s);
 // ensemble two-step: one block per list entry (member, 64-column tile x, tile y); lat < 0 = padding
 struct TwoTile {
   int32_t lat, txi, tyi, pad;

@@ -52,32 +52,27 @@ __device__ inline uint32_t tl_unknown(int x, int y, int nx, int ny) {
   return u;
 }
 
-// NSBC's vector m_c of boundary node (x, y) (eqs. nes_2, nes_3); `mom(xx,
-// yy, m)` returns the previous level's moments of any lattice node.  Same
-// order as the edge kernel: the x normal first (the vertical edges own the
-// corners), then the y normal.
+// NSBC's vector m_c of a boundary node (eqs. nes_2, nes_3) on NSBC edges whose
+// inward directions are dx and dy (+-1, 0: not on an NSBC edge of that axis; not both 0);
+// `mom(ax, ay, m)` returns the previous level's moments of the node (ax, ay)
+// away.  Same order as the edge kernel: the x normal first (the vertical edges
+// own the corners), then the y normal.
 template <class R, class MomFn>
-__device__ inline M3<R> tl_predict(const LatDesc& Ld, int x, int y, const Base<R>& b, MomFn mom) {
-  const int nx = Ld.nx, ny = Ld.ny;
-  const bool onL = x == 0, onR = x == nx - 1, onB = y == 0, onT = y == ny - 1;
-  R mb[3];
-  mom(x, y, mb);
-  R dsum[3] = {R(0), R(0), R(0)};
-  int nn = 0;
-  if (onL || onR) {
-    const int d = onL ? 1 : -1;
-    R m1[3], m2[3];
-    mom(x + d, y, m1);
-    mom(x + 2 * d, y, m2);
-    ++nn;
+__device__ inline M3<R> predict_at(const LatDesc& Ld, int dx, int dy, MomFn mom) {
+  R mb[3], m1[3], m2[3] = {R(0), R(0), R(0)}, dsum[3] = {R(0), R(0), R(0)};
+  const bool three = Ld.grad_order != 1;  // the two-point difference needs no third node
+  mom(0, 0, mb);
+  // the first normal along whichever axis it has: nodes of vertical and
+  // horizontal edges in one wavefront take one path
+  const int ax = dx, ay = dx ? 0 : dy;
+  mom(ax, ay, m1);
+  if (three) mom(2 * ax, 2 * ay, m2);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) dsum[c] += normal_diff(mb[c], m1[c], m2[c], Ld.grad_order);
-  }
-  if (onB || onT) {
-    const int d = onB ? 1 : -1;
-    R m1[3], m2[3];
-    mom(x, y + d, m1);
-    mom(x, y + 2 * d, m2);
+  for (int c = 0; c < 3; ++c) dsum[c] += normal_diff(mb[c], m1[c], m2[c], Ld.grad_order);
+  int nn = 1;
+  if (dx && dy) {  // corner
+    mom(0, dy, m1);
+    if (three) mom(0, 2 * dy, m2);
     ++nn;
 #pragma unroll
     for (int c = 0; c < 3; ++c) dsum[c] += normal_diff(mb[c], m1[c], m2[c], Ld.grad_order);
@@ -92,6 +87,14 @@ __device__ inline M3<R> tl_predict(const LatDesc& Ld, int x, int y, const Base<R
     mc.v[c] = (R(1) - beta) * mp + beta * R(Ld.m0[c]);
   }
   return mc;
+}
+
+// The same for node (x, y) of a lattice with four NSBC edges; `mom(xx, yy, m)`
+// takes lattice positions.
+template <class R, class MomFn>
+__device__ inline M3<R> tl_predict(const LatDesc& Ld, int x, int y, const Base<R>&, MomFn mom) {
+  const int dx = x == 0 ? 1 : (x == Ld.nx - 1 ? -1 : 0), dy = y == 0 ? 1 : (y == Ld.ny - 1 ? -1 : 0);
+  return predict_at<R>(Ld, dx, dy, [&](int ax, int ay, R m[3]) { mom(x + ax, y + ay, m); });
 }
 
 // NSBC of boundary node (x, y): unknown populations already zeroed and
