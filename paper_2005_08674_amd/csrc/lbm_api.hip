@@ -536,24 +536,29 @@ bool free_choice(const lbm_ctx* c) { return !c->chosen && !c->timing && use_fuse
 // FP32 (25 / 24 / 33) and trail or tie below (1024 x 1024: 14.9 / 15.8 / 14.4
 // and 8.3 / 9.2 / 8.7; in runs of 10, where three steps leave a remainder, the
 // deep sweep is ahead throughout); the 16-bit formats, whose deep sweep pays
-// for its conversions, change at 512^2 (3.7 / 6.2 / 3.9; 701^2: 4.4 / 6.5 / 5.7).
+// for its conversions, change at 2^19 nodes (512^2: 3.7 / 6.2 / 3.9, 701^2: 4.4 /
+// 6.5 / 5.7).
 int free_multi(const lbm_ctx* c) {
   const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
   const bool half = c->lay.esize == 2;
-  if (nodes < (half ? (int64_t)1 << 18 : (int64_t)1 << 21)) return -1;
+  if (nodes < (half ? (int64_t)1 << 19 : (int64_t)1 << 21)) return -1;
   const int id = multi_named(nodes < (int64_t)1 << 21 ? "3step:64x12/768+xcdband+nts"
                                                       : "3step:64x12/768+march11xh96+xcdband+nts");
   return multi_supported(c->L, id) ? id : -1;
 }
 
-// Deep-sweep shape of a free lattice: the smallest tile that leaves every
-// block a CU of its own, so that a level costs latency only (128^2 FP64: 2.1 us
-// a step with 8 x 8 tiles, 2.5 with 16 x 16; 256^2: 5.2 and 2.6); a larger
-// lattice takes the widest, which recomputes the least margin.  -1 if the
-// lattice is too small for it.
+// Deep-sweep shape of a free lattice: the smallest tile whose blocks are all
+// resident at once, so that a level costs latency only; a larger lattice takes
+// the widest, which recomputes the least margin.  -1 if the lattice is too small
+// for any.  us per step with 8 x 8, 16 x 16 and 32 x 16 tiles, runs of 10 on four
+// NSBC edges: FP32 (two blocks a CU or more) 128^2 1.63 / 1.89 / 2.76, 200^2
+// 1.84 / 1.87 / 2.77, 256^2 2.41 / 1.91 / 2.83, 512^2 5.56 / 3.68 / 4.10; FP64
+// (one block) 128^2 2.12 / 2.54 / 3.00, 256^2 5.22 / 2.53 / 3.06, 300^2 6.36 /
+// 3.47 / 3.12, 512^2 13.7 / 7.28 / 5.65.
 int deep_shape(const lbm_ctx* c) {
   int id = 0;
-  for (; id < lbm::num_deep() - 1 && lbm::deep_tiles(c->L, id) > 256; ++id) {
+  const bool f64 = c->p.store == LBM_STORE_F64;
+  for (; id < lbm::num_deep() - 1 && lbm::deep_tiles(c->L, id) > (f64 ? 256 : 512 << id); ++id) {
   }
   while (id >= 0 && !lbm::deep_supported(c->L, id)) --id;
   return id;

@@ -39,11 +39,13 @@ struct DeepShape {
   static constexpr int NT = NM + 64 * EW;
 };
 
-// Register budget: two blocks of the widest shape on a CU for the 32-bit
-// arithmetic (64 VGPRs; the perimeter path would take 93, and spills instead).
+// Register budget: two blocks of a wide shape on a CU for the 32-bit arithmetic
+// (64 VGPRs for 32 x 16, 80 for 16 x 16; the perimeter path would take 93 and
+// spills instead: 4096^2 FP32 162 -> 125 us a step, 512^2 with 16 x 16 tiles 5.0
+// -> 3.7).  FP64 needs its 127-149 (16 x 16 held to 80: 256^2 2.6 -> 3.2).
 template <int S, int NT>
 constexpr int deep_waves() {
-  return NT == 1024 && S != ST_F64 ? 8 : 1;
+  return S == ST_F64 ? 1 : (NT == 1024 ? 8 : (NT == 704 ? 6 : 1));
 }
 
 template <int S, int CM, bool UB0, int TX, int TY, int KM, bool NTS>

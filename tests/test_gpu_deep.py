@@ -45,14 +45,15 @@ def _check(a, b, runs):
 @pytest.mark.parametrize("bc", EDGES)
 def test_chosen_launches_equal_single_steps(store, bc):
     # 17: below the smallest tile's reach; 18: the smallest; then remainders of every tile, and sizes on
-    # both sides of 256 tiles of 8 x 8 and of 16 x 16
-    for nx, ny in ((17, 19), (18, 18), (26, 27), (41, 30), (61, 133), (128, 128), (129, 128), (250, 257), (300, 241)):
+    # both sides of 256 (FP64) or 512 tiles of 8 x 8 and of 256 or 1024 of 16 x 16
+    for nx, ny in ((17, 19), (18, 18), (26, 27), (41, 30), (61, 133), (128, 128), (129, 128), (181, 185), (250, 257),
+                   (300, 241), (520, 515)):
         for mrt, other in ((False, False), (True, False), (False, True)):
             a, b = _pair(nx, ny, store, bc, mrt, other)
             _check(a, b, (2, 5, 1, 9))
 
 
-@pytest.mark.parametrize("store,nx,ny", [("f16", 511, 512), ("bf16", 515, 513), ("f16", 2050, 1030),
+@pytest.mark.parametrize("store,nx,ny", [("f16", 723, 725), ("bf16", 733, 719), ("f16", 2050, 1030),
                                          ("f32", 2047, 1024), ("f32", 2050, 1030), ("f64", 2050, 1030)])
 def test_large_lattices_equal_single_steps(store, nx, ny):
     a, b = _pair(nx, ny, store, (1, 1, 1, 1), False, True)
