@@ -146,58 +146,26 @@ __device__ inline void node_moments3(const Lat3& L, const typename Codec<S>::T* 
   for (int a = 0; a < 3; ++a) m[1 + a] = j[a] * ir;
 }
 
-// Node on the lattice's outer shell: pulls wrap across periodic faces; a
-// population whose source lies beyond an NSBC face is unknown and rebuilt.
-// Written to keep few values live (no equilibrium or copy arrays: rebuilt
-// populations are formed in place from their opposites), so that the sweep
-// that carries it keeps the occupancy of its interior path.
+// Bit i set for every direction of the velocity set with c_axis = sign.
+template <int NQ>
+__host__ __device__ constexpr uint32_t dirs3(int axis, int sign) {
+  uint32_t m = 0;
+  for (int i = 0; i < NQ; ++i)
+    if (kC[i][axis] == sign) m |= 1u << i;
+  return m;
+}
+
+// NSBC of a node whose streamed populations are g, those of `unknown` lying
+// beyond an NSBC face: mb its moments at time t, d the sum of the differences
+// mb - (inner neighbour's moments) over the k NSBC faces it is on.  Written to
+// keep few values live (no equilibrium or copy arrays: rebuilt populations are
+// formed in place from their opposites), so that the sweep that carries it keeps
+// the occupancy of its interior path.
 template <int S, int NQ>
-__device__ inline void boundary_node3(const Lat3& L, const typename Codec<S>::T* A, int x, int y, int z,
-                                      typename Codec<S>::R g[NQ]) {
-  using C = Codec<S>;
-  using T = typename C::T;
-  using R = typename C::R;
-  const int n[3] = {L.nx, L.ny, L.nz}, p[3] = {x, y, z};
-  const uint32_t stride[3] = {1u, (uint32_t)L.pitch, (uint32_t)L.slab};
-  uint32_t unknown = 0;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    uint32_t src = 0;
-    bool out = false;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      int s = p[a] - kC[i][a];
-      if (s < 0 || s >= n[a]) {
-        if (L.bc[2 * a] == BC_PERIODIC) {
-          s = s < 0 ? s + n[a] : s - n[a];
-        } else {
-          out = true;
-          s = p[a];  // any node in range: the value is replaced below
-        }
-      }
-      src += (uint32_t)s * stride[a];
-    }
-    unknown |= (uint32_t)out << i;
-    g[i] = C::dec(*reinterpret_cast<const T*>(reinterpret_cast<const char*>(A + i * L.plane) + src * sizeof(T)),
-                  L.ds[i]);
-  }
-  if (!unknown) return;
-  // eq. nes_2 with the normalised normal of the k NSBC faces the node is on
-  const uint32_t own = ((uint32_t)z * stride[2] + (uint32_t)y * stride[1] + (uint32_t)x) * (uint32_t)sizeof(T);
-  R mb[4], d[4] = {R(0), R(0), R(0), R(0)};
-  node_moments3<S, NQ>(L, A, own, mb);
-  int k = 0;
-#pragma unroll 1
-  for (int a = 0; a < 3; ++a) {
-    if (L.bc[2 * a] != BC_NSBC) continue;
-    const int step = p[a] == 0 ? 1 : (p[a] == n[a] - 1 ? -1 : 0);
-    if (!step) continue;
-    R mn[4];
-    node_moments3<S, NQ>(L, A, own + (uint32_t)(step * (int)sizeof(T)) * stride[a], mn);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) d[c] += mb[c] - mn[c];
-    ++k;
-  }
+__device__ inline void shell_nsbc3(const Lat3& L, uint32_t unknown, const typename Codec<S>::R mb[4],
+                                   const typename Codec<S>::R d[4], int k, typename Codec<S>::R g[NQ]) {
+  using R = typename Codec<S>::R;
+  // eq. nes_2 with the normalised normal of the k faces
   const R fac = R(L.gamma) * (k == 1 ? R(1) : (k == 2 ? R(0.70710678118654752440) : R(0.57735026918962576451)));
   const R beta = R(L.beta);
   R mc[4];
@@ -208,15 +176,18 @@ __device__ inline void boundary_node3(const Lat3& L, const typename Codec<S>::T*
   const R rc = R(L.rho0) + mc[0];
   const R uu = R(1.5) * (mc[1] * mc[1] + mc[2] * mc[2] + mc[3] * mc[3]);
 #pragma unroll
-  for (int i = 1; i < NQ; ++i) {
-    if (!((unknown >> i) & 1u)) continue;
-    const int o = i & 1 ? i + 1 : i - 1;
+  for (int p = 1; p < NQ; p += 2) {
     R cu = R(0);
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-      if (kC[i][a]) cu += kC[i][a] > 0 ? mc[1 + a] : -mc[1 + a];
-    g[i] = (unknown >> o) & 1u ? w3<NQ, R>(i) * (mc[0] + rc * fma(cu, fma(R(4.5), cu, R(3)), -uu))
-                               : fma(R(6) * w3<NQ, R>(i) * rc, cu, g[o]);
+      if (kC[p][a]) cu += kC[p][a] > 0 ? mc[1 + a] : -mc[1 + a];
+    const bool up = (unknown >> p) & 1u, uo = (unknown >> (p + 1)) & 1u;
+    const R t = R(6) * w3<NQ, R>(p) * rc;
+    const R fp = up && uo ? w3<NQ, R>(p) * (mc[0] + rc * fma(cu, fma(R(4.5), cu, R(3)), -uu)) : fma(t, cu, g[p + 1]);
+    const R fo = up && uo ? w3<NQ, R>(p) * (mc[0] + rc * fma(-cu, fma(R(4.5), -cu, R(3)), -uu)) : fma(t, -cu, g[p]);
+    const R gp = up ? fp : g[p];
+    g[p + 1] = uo ? fo : g[p + 1];
+    g[p] = gp;
   }
   // eq. nes_4 with 1/c_s^2 = 3: shift all populations so the node carries m_c
   R s = R(0), j[3] = {R(0), R(0), R(0)};
@@ -241,11 +212,121 @@ __device__ inline void boundary_node3(const Lat3& L, const typename Codec<S>::T*
   }
 }
 
+// Rows on a y or z face (y = 0, ny - 1 for every z; z = 0, nz - 1 for the other
+// y), 64 nodes per block, as the first blocks of a step's launch.  A node needs
+// its q pulls and the moments at time t of itself and of its inner neighbour
+// along each NSBC face it is on: up to 5 q loads, whose round trips, one after
+// the other, were most of a launch of its own (19 us at 97 x 80 x 65 D3Q27 BF16,
+// the sweep 31; 17 of 496 at 256^3 D3Q19 FP32).  The block's wavefronts take
+// them side by side -- the pulls, the node's own moments, the neighbours' -- and
+// meet in LDS; with the loads spread this way the path also needs no more
+// registers than the sweep it shares the launch with.
+template <class R>
+struct FaceLds {
+  R m[4][4][64];  // moments of the node and of its x, y and z neighbour
+};
+__host__ __device__ inline int face_rows3(int ny, int nz) { return 2 * nz + 2 * (ny - 2); }
+__host__ __device__ inline int face_blocks3(int nx, int ny, int nz) {
+  return (face_rows3(ny, nz) * ((nx + 63) / 64) + 7) / 8 * 8;  // (a multiple of 8: the sweep's XCD map)
+}
+
+template <int S, int NQ, int NT>
+__device__ inline void face_block3(const Lat3& L, int parity, int fb, FaceLds<typename Codec<S>::R>& lds) {
+  using C = Codec<S>;
+  using T = typename C::T;
+  using R = typename C::R;
+  constexpr int NW = NT / 64;
+  const int nx = L.nx, ny = L.ny, nz = L.nz;
+  const int segs = (nx + 63) / 64, r = fb / segs;
+  if (r >= face_rows3(ny, nz)) return;  // padding: the whole block, before the barrier
+  int y, z;
+  if (r < 2 * nz) {
+    z = r >> 1;
+    y = r & 1 ? ny - 1 : 0;
+  } else {
+    const int k = r - 2 * nz;
+    y = 1 + (k >> 1);
+    z = k & 1 ? nz - 1 : 0;
+  }
+  const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int x = (fb - r * segs) * 64 + l;
+  const T* __restrict__ A = static_cast<const T*>(parity ? L.buf[1] : L.buf[0]);
+  const int n[3] = {nx, ny, nz}, p[3] = {min(x, nx - 1), y, z};  // (lanes beyond the row repeat its last node)
+  const uint32_t stride[3] = {(uint32_t)sizeof(T), (uint32_t)L.pitch * (uint32_t)sizeof(T),
+                              (uint32_t)L.slab * (uint32_t)sizeof(T)};
+  const uint32_t own = (uint32_t)p[2] * stride[2] + (uint32_t)p[1] * stride[1] + (uint32_t)p[0] * stride[0];
+  // step to the inner neighbour along each NSBC face (0: not on one)
+  int in[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) in[a] = L.bc[2 * a] != BC_NSBC ? 0 : (p[a] == 0 ? 1 : (p[a] == n[a] - 1 ? -1 : 0));
+  auto moments_to = [&](int slot, uint32_t off) {
+    R m[4];
+    node_moments3<S, NQ>(L, A, off, m);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lds.m[slot][c][l] = m[c];
+  };
+  // tasks: 1 the node's moments, 2 the first of its y and z neighbours (the
+  // same for the whole row), 3 the second of them and, at the row's ends, the x one
+  auto neighbour = [&](int a) { moments_to(1 + a, own + (uint32_t)(in[a] * (int)stride[a])); };
+  if (w == 1 % NW && (in[0] | in[1] | in[2])) moments_to(0, own);
+  if (w == 2 % NW) {
+    if (in[1]) neighbour(1);
+    else if (in[2]) neighbour(2);
+  }
+  if (w == 3 % NW) {
+    if (in[1] && in[2]) neighbour(2);
+    if (in[0]) neighbour(0);
+  }
+  // the pulls: sources wrapped across periodic faces, or the node's own
+  // coordinate beyond an NSBC face (the value is replaced)
+  uint32_t unknown = 0;
+  R g[NQ];
+  if (w == 0) {
+    uint32_t src[3][3];  // byte offset of coordinate p - 1, p, p + 1 along each axis
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const bool per = L.bc[2 * a] == BC_PERIODIC, lo = p[a] == 0, hi = p[a] == n[a] - 1;
+      src[a][0] = (uint32_t)(lo ? (per ? n[a] - 1 : p[a]) : p[a] - 1) * stride[a];
+      src[a][1] = (uint32_t)p[a] * stride[a];
+      src[a][2] = (uint32_t)(hi ? (per ? 0 : p[a]) : p[a] + 1) * stride[a];
+      if (lo && !per) unknown |= dirs3<NQ>(a, 1);
+      if (hi && !per) unknown |= dirs3<NQ>(a, -1);
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const uint32_t off = src[0][1 - kC[i][0]] + src[1][1 - kC[i][1]] + src[2][1 - kC[i][2]];
+      g[i] = C::dec(*reinterpret_cast<const T*>(reinterpret_cast<const char*>(A + i * L.plane) + off), L.ds[i]);
+    }
+  }
+  __syncthreads();
+  if (w != 0 || x >= nx) return;
+  if (unknown) {
+    R mb[4], d[4] = {R(0), R(0), R(0), R(0)};
+    int k = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) mb[c] = lds.m[0][c][l];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (!in[a]) continue;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) d[c] += mb[c] - lds.m[1 + a][c][l];
+      ++k;
+    }
+    shell_nsbc3<S, NQ>(L, unknown, mb, d, k, g);
+  }
+  bgk3<NQ, R>(g, R(L.rho0), R(L.omega));
+  T* __restrict__ B = static_cast<T*>(parity ? L.buf[0] : L.buf[1]);
+#pragma unroll
+  for (int i = 0; i < NQ; ++i)
+    __builtin_nontemporal_store(C::enc(g[i], L.es[i]), reinterpret_cast<T*>(reinterpret_cast<char*>(B + i * L.plane) + own));
+}
+
 // NSBC on an x face, for a node whose y and z neighbours all lie inside: `g`
 // holds its pulls with the unknown ones (c_x = side, side = +1 at x = 0 and
 // -1 at x = nx - 1) loaded from any node in range; mb and mn are the moments
 // at time t of the node and of its inner x neighbour.  Same arithmetic as
-// boundary_node3 with k = 1.
+// shell_nsbc3 with k = 1.
 template <int S, int NQ>
 __device__ inline void xface_nsbc3(const Lat3& L, const typename Codec<S>::R mb[4],
                                    const typename Codec<S>::R mn[4], int side, typename Codec<S>::R g[NQ]) {
@@ -321,9 +402,8 @@ __device__ __forceinline__ void pull_row3(const Lat3& L, const typename Codec<S>
 // list of (z chunk, tile row, tile column) in that order, so XCD k (blocks
 // b = k mod 8) works through the k-th contiguous stretch: x-neighbouring
 // tiles, which share the lines their shifted pulls straddle, run on one XCD.
-// Rows on a y or z face are left to a second launch (k3_faces, node by node
-// with boundary_node3), so that their registers do not weigh on this kernel.
-// In the other rows an x-face node is one lane of
+// Rows on a y or z face are left to the launch's first `faces` blocks
+// (face_block3).  In the other rows an x-face node is one lane of
 // a wavefront: it pulls with the others (the x shift adjusted), and on a NSBC
 // face it takes the moments at time t of itself and of its inner neighbour
 // from Lat3::mx instead of loading 2 q stored populations: the lanes of those
@@ -334,13 +414,18 @@ __device__ __forceinline__ void pull_row3(const Lat3& L, const typename Codec<S>
 // no cache line of the output is written in parts by different blocks.
 template <int S, int NQ, int BX, int BY, int ZC, bool NTL>
 __global__ __launch_bounds__(BX* BY, (k3_waves<S, NQ>())) void k3_step(Lat3 L, int parity, int tiles_x, int tiles_y,
-                                                                int nitems, int per) {
+                                                                int nitems, int per, int faces) {
   using C = Codec<S>;
   using T = typename C::T;
   using R = typename C::R;
-  const int b = blockIdx.x;
+  __shared__ FaceLds<R> lds;
+  if ((int)blockIdx.x < faces) {
+    face_block3<S, NQ, BX * BY>(L, parity, blockIdx.x, lds);
+    return;
+  }
+  const int b = blockIdx.x - faces;
   const int item = (b & 7) * per + (b >> 3);
-  if (item >= nitems) return;  // no barrier in this kernel
+  if (item >= nitems) return;  // (no barrier from here on)
   const int ntile = tiles_x * tiles_y;
   const int zc = item / ntile, t = item - zc * ntile;
   const int ty = t / tiles_x, tx = t - ty * tiles_x;
@@ -368,7 +453,7 @@ __global__ __launch_bounds__(BX* BY, (k3_waves<S, NQ>())) void k3_step(Lat3 L, i
     R g[NQ];
     const uint32_t idx = (uint32_t)((int64_t)z * L.slab + (int64_t)y * L.pitch + x);
     const bool inner_row = y_inner && z >= 1 && z <= nz - 2;
-    if (!inner_row) continue;  // rows on a y or z face: k3_faces
+    if (!inner_row) continue;  // rows on a y or z face: face_block3
     {
       pull_row3<S, NQ, NTL>(L, A, idx, sxm, sxp, g);
       if (xside) {
@@ -418,7 +503,7 @@ __global__ __launch_bounds__(BX* BY, (k3_waves<S, NQ>())) void k3_step(Lat3 L, i
 // bytes in flight.  Per node the pulls, the functions and their order are the
 // one-node sweep's (an x-face node takes its unknown pulls from itself, as
 // there), so the results are bit-identical.  The rows on a y or z face go to
-// a second, node-by-node launch (k3_faces).  Lattices with periodic x faces or
+// the launch's first blocks (face_block3).  Lattices with periodic x faces or
 // an odd nx take the one-node sweep.
 template <class T>
 __device__ inline T from_bits16(uint32_t h) {
@@ -437,14 +522,19 @@ constexpr int k3_pair_waves() {
 
 template <int S, int NQ, int BX, int BY, int ZC>
 __global__ __launch_bounds__(BX* BY, (k3_pair_waves<NQ>())) void k3_pair(Lat3 L, int parity, int tiles_x, int tiles_y,
-                                                                int nitems, int per) {
+                                                                int nitems, int per, int faces) {
   using C = Codec<S>;
   using T = typename C::T;
   using R = typename C::R;
   static_assert(sizeof(T) == 2, "the pair sweep is for the 16-bit formats");
-  const int b = blockIdx.x;
+  __shared__ FaceLds<R> lds;
+  if ((int)blockIdx.x < faces) {
+    face_block3<S, NQ, BX * BY>(L, parity, blockIdx.x, lds);
+    return;
+  }
+  const int b = blockIdx.x - faces;
   const int item = (b & 7) * per + (b >> 3);
-  if (item >= nitems) return;  // no barrier in this kernel
+  if (item >= nitems) return;  // (no barrier from here on)
   const int ntile = tiles_x * tiles_y;
   const int zc = item / ntile, t = item - zc * ntile;
   const int ty = t / tiles_x, tx = t - ty * tiles_x;
@@ -531,41 +621,8 @@ __global__ __launch_bounds__(BX* BY, (k3_pair_waves<NQ>())) void k3_pair(Lat3 L,
       for (int i = 0; i < NQ; ++i)
         __builtin_nontemporal_store(w[i], reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(B + i * L.plane) + off));
     }
-    // (rows on a y or z face: k3_faces)
+    // (rows on a y or z face: face_block3)
   }
-}
-
-// The rows on a y or z face (y = 0, ny - 1 for every z; z = 0, nz - 1 for the
-// other y), node by node with boundary_node3, one block per row segment of
-// 256 nodes; launched after k3_step or k3_pair, which leave them out so that
-// their registers do not weigh on them.
-template <int S, int NQ>
-__global__ __launch_bounds__(256) void k3_faces(Lat3 L, int parity) {
-  using C = Codec<S>;
-  using T = typename C::T;
-  using R = typename C::R;
-  const int nx = L.nx, ny = L.ny, nz = L.nz;
-  const int r = blockIdx.y;  // face row: 0 .. 2 nz - 1 on the y faces, then 2 (ny - 2) on the z faces
-  int y, z;
-  if (r < 2 * nz) {
-    z = r >> 1;
-    y = r & 1 ? ny - 1 : 0;
-  } else {
-    const int k = r - 2 * nz;
-    y = 1 + (k >> 1);
-    z = k & 1 ? nz - 1 : 0;
-  }
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= nx) return;
-  const T* __restrict__ A = static_cast<const T*>(parity ? L.buf[1] : L.buf[0]);
-  T* __restrict__ B = static_cast<T*>(parity ? L.buf[0] : L.buf[1]);
-  R g[NQ];
-  boundary_node3<S, NQ>(L, A, x, y, z, g);
-  bgk3<NQ, R>(g, R(L.rho0), R(L.omega));
-  const uint32_t off = (uint32_t)((int64_t)z * L.slab + (int64_t)y * L.pitch + x) * (uint32_t)sizeof(T);
-#pragma unroll
-  for (int i = 0; i < NQ; ++i)
-    __builtin_nontemporal_store(C::enc(g[i], L.es[i]), reinterpret_cast<T*>(reinterpret_cast<char*>(B + i * L.plane) + off));
 }
 
 // Launch shapes: block BX x BY, ZC z-planes per block, non-temporal pull
@@ -624,10 +681,9 @@ template <int S, int NQ, int BX, int BY, int ZC, bool NTL>
 static hipError_t launch3_t(const Lat3& L, int parity, hipStream_t s) {
   const int tiles_x = (L.nx + BX - 1) / BX, tiles_y = (L.ny + BY - 1) / BY, zch = (L.nz + ZC - 1) / ZC;
   const int nitems = tiles_x * tiles_y * zch, per = (nitems + 7) / 8;
-  k3_step<S, NQ, BX, BY, ZC, NTL><<<dim3(8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k3_faces<S, NQ><<<dim3((L.nx + 255) / 256, 2 * L.nz + 2 * (L.ny - 2)), dim3(256), 0, s>>>(L, parity);
+  const int faces = face_blocks3(L.nx, L.ny, L.nz);
+  k3_step<S, NQ, BX, BY, ZC, NTL>
+      <<<dim3(faces + 8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per, faces);
   return hipGetLastError();
 }
 
@@ -636,10 +692,9 @@ static hipError_t launch3_pair_t(const Lat3& L, int parity, hipStream_t s) {
   if constexpr (S == ST_F16 || S == ST_BF16) {
     const int tiles_x = (L.nx / 2 + BX - 1) / BX, tiles_y = (L.ny + BY - 1) / BY, zch = (L.nz + ZC - 1) / ZC;
     const int nitems = tiles_x * tiles_y * zch, per = (nitems + 7) / 8;
-    k3_pair<S, NQ, BX, BY, ZC><<<dim3(8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k3_faces<S, NQ><<<dim3((L.nx + 255) / 256, 2 * L.nz + 2 * (L.ny - 2)), dim3(256), 0, s>>>(L, parity);
+    const int faces = face_blocks3(L.nx, L.ny, L.nz);
+    k3_pair<S, NQ, BX, BY, ZC>
+        <<<dim3(faces + 8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per, faces);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
