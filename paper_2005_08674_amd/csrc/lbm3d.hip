@@ -398,10 +398,26 @@ __device__ __forceinline__ void pull_row3(const Lat3& L, const typename Codec<S>
   }
 }
 
-// One launch per step.  Block b takes item (b mod 8) * per + b / 8 of the
-// list of (z chunk, tile row, tile column) in that order, so XCD k (blocks
-// b = k mod 8) works through the k-th contiguous stretch: x-neighbouring
-// tiles, which share the lines their shifted pulls straddle, run on one XCD.
+// Item of block b in the list of (z chunk, tile row, tile column): blocks go to
+// the 8 XCDs round-robin (b mod 8), and in each run of 8 RUN items XCD k takes
+// RUN consecutive ones.  x-neighbouring tiles, which share the lines their
+// shifted pulls straddle, thus mostly run on one XCD, and the eight XCDs stream
+// through the same few planes: with a contiguous eighth of the list each, eight
+// regions were open in memory at a time (256^3 FP32 D3Q19, 128 x 1 blocks: 485 ->
+// 470 us a step; D3Q19 BF16 pairs 266 -> 246; RUN 1 to 64 are within 3 % from 4 to
+// 16 on).  A block as wide as the row shares no lines, and prefers the short run
+// (RUN 2 460, 8 466, 32 478 us).
+template <int BX>
+__host__ __device__ constexpr int run3() {
+  return BX >= 256 ? 2 : 8;
+}
+template <int BX>
+__device__ inline int item3(int b) {
+  constexpr int R = run3<BX>();
+  return (b & ~(8 * R - 1)) + (b & 7) * R + ((b >> 3) & (R - 1));
+}
+
+// One launch per step, a block per item of the list (item3).
 // Rows on a y or z face are left to the launch's first `faces` blocks
 // (face_block3).  In the other rows an x-face node is one lane of
 // a wavefront: it pulls with the others (the x shift adjusted), and on a NSBC
@@ -414,7 +430,7 @@ __device__ __forceinline__ void pull_row3(const Lat3& L, const typename Codec<S>
 // no cache line of the output is written in parts by different blocks.
 template <int S, int NQ, int BX, int BY, int ZC, bool NTL>
 __global__ __launch_bounds__(BX* BY, (k3_waves<S, NQ>())) void k3_step(Lat3 L, int parity, int tiles_x, int tiles_y,
-                                                                int nitems, int per, int faces) {
+                                                                int nitems, int faces) {
   using C = Codec<S>;
   using T = typename C::T;
   using R = typename C::R;
@@ -424,7 +440,7 @@ __global__ __launch_bounds__(BX* BY, (k3_waves<S, NQ>())) void k3_step(Lat3 L, i
     return;
   }
   const int b = blockIdx.x - faces;
-  const int item = (b & 7) * per + (b >> 3);
+  const int item = item3<BX>(b);
   if (item >= nitems) return;  // (no barrier from here on)
   const int ntile = tiles_x * tiles_y;
   const int zc = item / ntile, t = item - zc * ntile;
@@ -522,7 +538,7 @@ constexpr int k3_pair_waves() {
 
 template <int S, int NQ, int BX, int BY, int ZC>
 __global__ __launch_bounds__(BX* BY, (k3_pair_waves<NQ>())) void k3_pair(Lat3 L, int parity, int tiles_x, int tiles_y,
-                                                                int nitems, int per, int faces) {
+                                                                int nitems, int faces) {
   using C = Codec<S>;
   using T = typename C::T;
   using R = typename C::R;
@@ -533,7 +549,7 @@ __global__ __launch_bounds__(BX* BY, (k3_pair_waves<NQ>())) void k3_pair(Lat3 L,
     return;
   }
   const int b = blockIdx.x - faces;
-  const int item = (b & 7) * per + (b >> 3);
+  const int item = item3<BX>(b);
   if (item >= nitems) return;  // (no barrier from here on)
   const int ntile = tiles_x * tiles_y;
   const int zc = item / ntile, t = item - zc * ntile;
@@ -667,23 +683,54 @@ static const ShapePair kPairs3[] = {
 #undef X
 };
 static constexpr int kNumPairs3 = sizeof(kPairs3) / sizeof(kPairs3[0]);
-static constexpr int kNumAll3 = kNumShapes3 + kNumPairs3;
+
+// One-node shapes of whole rows (ids from kNumShapes3 + kNumPairs3 on).
+#define LBM3D_ROW_SHAPES(X) \
+  X(256, 1, 1, false)
+static const Shape3 kRows3[] = {
+#define X(a, b, c, d) {a, b, c, d},
+    LBM3D_ROW_SHAPES(X)
+#undef X
+};
+static constexpr int kNumRows3 = sizeof(kRows3) / sizeof(kRows3[0]);
+static constexpr int kFirstRow3 = kNumShapes3 + kNumPairs3;
+static constexpr int kNumAll3 = kFirstRow3 + kNumRows3;
 
 // Whether launch shape `id` takes lattice L: the pair shapes need a 16-bit
 // format, non-periodic x faces and an even nx.
 static bool shape3_supported(const Lat3& L, int id) {
   if (id < 0 || id >= kNumAll3) return false;
-  if (id < kNumShapes3) return true;
+  if (id < kNumShapes3 || id >= kFirstRow3) return true;
   return (L.store == ST_F16 || L.store == ST_BF16) && L.bc[0] != BC_PERIODIC && L.nx % 2 == 0;
+}
+
+// Shape of a lattice nobody has chosen one for.  us per step at 97 x 80 x 65
+// D3Q27, 200 x 150 x 100 D3Q27 and 256^3 D3Q19: FP32 30 / 142 / 476 with 64 x 4
+// blocks, 31 / 141 / 460 with whole rows; BF16 36 / 167 / 459 with 64 x 4 and 31 / 133 /
+// 396 with 64 x 2 one-node blocks, - / 96 / 247 and - / 90 / 249 with pairs in 64 x 2
+// and 128 x 1 blocks (64 wide, D3Q27 FP16: 17.9 one-node 64 x 2, 18.8 pairs).  The wider
+// block is taken where it leaves no more lanes idle.
+static int default_shape3(const Lat3& L) {
+  auto find = [](auto& list, int bx, int by, int zc) {
+    int i = 0;
+    while (list[i].bx != bx || list[i].by != by || list[i].zc != zc) ++i;
+    return i;
+  };
+  auto wide = [](int n, int b) { return (n + b - 1) / b * b <= (n + 63) / 64 * 64; };
+  if (L.store == ST_F16 || L.store == ST_BF16) {
+    const int pair = kNumShapes3 + (wide(L.nx / 2, 128) ? find(kPairs3, 128, 1, 1) : find(kPairs3, 64, 2, 1));
+    return L.nx > 64 && shape3_supported(L, pair) ? pair : find(kShapes3, 64, 2, 1);
+  }
+  return wide(L.nx, 256) ? kFirstRow3 : find(kShapes3, 64, 4, 1);
 }
 
 template <int S, int NQ, int BX, int BY, int ZC, bool NTL>
 static hipError_t launch3_t(const Lat3& L, int parity, hipStream_t s) {
   const int tiles_x = (L.nx + BX - 1) / BX, tiles_y = (L.ny + BY - 1) / BY, zch = (L.nz + ZC - 1) / ZC;
-  const int nitems = tiles_x * tiles_y * zch, per = (nitems + 7) / 8;
+  const int nitems = tiles_x * tiles_y * zch, run = 8 * run3<BX>();
   const int faces = face_blocks3(L.nx, L.ny, L.nz);
   k3_step<S, NQ, BX, BY, ZC, NTL>
-      <<<dim3(faces + 8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per, faces);
+      <<<dim3(faces + (nitems + run - 1) / run * run), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, faces);
   return hipGetLastError();
 }
 
@@ -691,10 +738,10 @@ template <int S, int NQ, int BX, int BY, int ZC>
 static hipError_t launch3_pair_t(const Lat3& L, int parity, hipStream_t s) {
   if constexpr (S == ST_F16 || S == ST_BF16) {
     const int tiles_x = (L.nx / 2 + BX - 1) / BX, tiles_y = (L.ny + BY - 1) / BY, zch = (L.nz + ZC - 1) / ZC;
-    const int nitems = tiles_x * tiles_y * zch, per = (nitems + 7) / 8;
+    const int nitems = tiles_x * tiles_y * zch, run = 8 * run3<BX>();
     const int faces = face_blocks3(L.nx, L.ny, L.nz);
     k3_pair<S, NQ, BX, BY, ZC>
-        <<<dim3(faces + 8 * per), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, per, faces);
+        <<<dim3(faces + (nitems + run - 1) / run * run), dim3(BX, BY), 0, s>>>(L, parity, tiles_x, tiles_y, nitems, faces);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -714,6 +761,11 @@ static hipError_t launch3_s(const Lat3& L, int parity, int shape, hipStream_t s)
   if (shape == k) return launch3_pair_t<S, NQ, a, b, c>(L, parity, s);  \
   ++k;
   LBM3D_PAIR_SHAPES(X)
+#undef X
+#define X(a, b, c, d)                                                    \
+  if (shape == k) return launch3_t<S, NQ, a, b, c, d>(L, parity, s);    \
+  ++k;
+  LBM3D_ROW_SHAPES(X)
 #undef X
   return hipErrorInvalidValue;
 }
@@ -934,7 +986,7 @@ struct lbm3d_ctx {
   lbm::d3::Lat3 L;
   int parity = 0;
   int64_t t = 0;
-  int shape = 4;  // 128x1xz1, the fastest on 256^3 in both formats
+  int shape = 0;  // default_shape3 at init
   hipStream_t stream = nullptr;
   int* flag = nullptr;    // device int in the workspace (lbm3d_check_finite)
   float* part = nullptr;  // 256 device floats in the workspace (FP16 exponent at init)
@@ -1079,6 +1131,7 @@ int lbm3d_init(lbm3d_ctx** out, const lbm3d_params* p, void* workspace, size_t b
     k = lbm::host::f16_exp_from_max(mx);
   }
   c->f16_exp = k;
+  c->shape = lbm::d3::default_shape3(L);
   for (int i = 0; i < 27; ++i) {
     const double w = L.q == 27 ? lbm::d3::w3<27, double>(i) : (i < 19 ? lbm::d3::w3<19, double>(i) : 1.0);
     const bool scaled = p->store == LBM_STORE_F16DEV || p->store == LBM_STORE_BF16DEV;
@@ -1165,12 +1218,12 @@ int lbm3d_shape_count(void) { return lbm::d3::kNumAll3; }
 int lbm3d_shape_describe(int32_t id, char* buf, size_t len) {
   if (!buf || len == 0) return fail(LBM_ERR_ARG, "NULL buffer");
   if (id < 0 || id >= lbm::d3::kNumAll3) return fail(LBM_ERR_ARG, "shape id %d out of range", id);
-  if (id >= lbm::d3::kNumShapes3) {
+  if (id >= lbm::d3::kNumShapes3 && id < lbm::d3::kFirstRow3) {
     const lbm::d3::ShapePair& s = lbm::d3::kPairs3[id - lbm::d3::kNumShapes3];
     snprintf(buf, len, "pair:%dx%dxz%d", s.bx, s.by, s.zc);
     return LBM_OK;
   }
-  const lbm::d3::Shape3& s = lbm::d3::kShapes3[id];
+  const lbm::d3::Shape3& s = id < lbm::d3::kNumShapes3 ? lbm::d3::kShapes3[id] : lbm::d3::kRows3[id - lbm::d3::kFirstRow3];
   snprintf(buf, len, "%dx%dxz%d%s", s.bx, s.by, s.zc, s.ntl ? "+ntl" : "");
   return LBM_OK;
 }
