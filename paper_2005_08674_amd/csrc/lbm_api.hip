@@ -719,6 +719,8 @@ int lbm_step(lbm_ctx* c, int32_t n) {
     if (rc == LBM_OK && n - s >= 2) {
       const int r = rem_shape(c, n - s);
       if (r >= 0) {
+        // (another shape's edge tiles may reach past this one's border)
+        HIPCHK(settle_join(c, c->join_pending));
         rc = step_multi(c, r);
         s += multi_steps(r);
       }

@@ -114,8 +114,9 @@ __device__ inline void bias_tanh_store(const f32x4 acc[NT], const float* bias, b
   for (int n = 0; n < NT; ++n) {
     const int col = 16 * n + (l & 15);
     const float b = bias[col];
+    const bf16x4 t = tanh_bf16(acc[n] + f32x4{b, b, b, b});
 #pragma unroll
-    for (int r = 0; r < 4; ++r) H[(4 * (l >> 4) + r) * hs + col] = (bf16)tanhf(acc[n][r] + b);
+    for (int r = 0; r < 4; ++r) H[(4 * (l >> 4) + r) * hs + col] = t[r];
   }
 }
 
@@ -181,6 +182,51 @@ __device__ inline void forward16(const Params& p, const bf16* X, bf16* H1, bf16*
 }
 __device__ inline void forward16(const Net& net, const bf16* X, bf16* H1, bf16* H2, f32x4& y) {
   forward16(params_of(net), X, H1, H2, y);
+}
+
+// The weights as this lane's MFMA operands (88 registers), loaded ahead of the
+// rows they are used for, and the forward pass with them: forward16's result.
+struct Frags {
+  bf16x8 w1[IN / 32][4], w2[HID / 32][4], w3[HID / 32];
+};
+__device__ inline void load_frags(const Net& net, Frags& f) {
+#pragma unroll
+  for (int kt = 0; kt < IN / 32; ++kt)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) f.w1[kt][n] = frag_k1(net.W1, IN, 16 * n, 32 * kt);
+#pragma unroll
+  for (int kt = 0; kt < HID / 32; ++kt) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) f.w2[kt][n] = frag_k1(net.W2, HID, 16 * n, 32 * kt);
+    f.w3[kt] = frag_k1(net.W3, HID, 0, 32 * kt);
+  }
+}
+template <int KT>
+__device__ inline void layer(const bf16* X, int xs, const bf16x8 (&w)[KT][4], f32x4 acc[4]) {
+#pragma unroll
+  for (int n = 0; n < 4; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) {
+    const bf16x8 a = frag_k1(X, xs, 0, 32 * kt);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[n] = mfma(a, w[kt][n], acc[n]);
+  }
+}
+__device__ inline void forward16(const Frags& f, const Params& p, const bf16* X, bf16* H1, bf16* H2, f32x4& y) {
+  f32x4 a[4];
+  layer(X, XS, f.w1, a);
+  bias_tanh_store<4>(a, p.b1, H1, HS);
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_s_waitcnt(0);
+  layer(H1, HS, f.w2, a);
+  bias_tanh_store<4>(a, p.b2, H2, HS);
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_s_waitcnt(0);
+  f32x4 a3 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < HID / 32; ++kt) a3 = mfma(frag_k1(H2, HS, 0, 32 * kt), f.w3[kt], a3);
+  const float b = p.b3[lane() & 15];
+  y = a3 + f32x4{b, b, b, b};
 }
 
 }  // namespace mlp

@@ -70,7 +70,7 @@ constexpr bool three_step_fits_closure() {
 // the registers the network wants.
 template <int S, bool CL>
 constexpr int three_step_waves() {
-  return CL ? 2 : two_step_waves<S>();
+  return CL ? (S == ST_F64 ? 1 : 2) : two_step_waves<S>();
 }
 
 // The inner tiles of a lattice form the rectangle txi in [1, ix], tyi in
@@ -102,23 +102,77 @@ __host__ __device__ inline bool ring_tile(int b, int tiles_x, int tiles_y, int i
 __host__ __device__ inline int inner_cols(int nx) { return nx >= 67 ? (nx - 67) / TL_TX : 0; }
 __host__ __device__ inline int inner_rows(int ny, int ty) { return ny >= ty + 3 ? (ny - ty - 3) / ty : 0; }
 
+// Geometry of a marched sweep with tiles of TY rows: the edge tiles are one row
+// of 64 x TY tiles along the bottom and one along the top, and between them one
+// column of EDGE_TX x 4 TY tiles along each side (the last of a row or column moved
+// back to end with it).  A side tile's network and NSBC nodes sit in one column,
+// so a 64-wide tile there spent its time on 63 columns of interior nodes: with
+// narrow ones 2048^2 has 150 edge tiles instead of 402, 4096^2 298 instead of 808.
+// The strips march over the rest, columns EDGE_TX .. nx - EDGE_TX - 1 and rows TY ..
+// ny - TY - 1.  Strip sx starts at column 64 sx, whole cache lines in every format;
+// the first is moved on to EDGE_TX and the last back to end at nx - EDGE_TX (the
+// overlaps hold the same values in both).  Strips from column 16 on wrote parts of
+// lines (4096^2 us per step FP16 61 -> 83, FP32 80 -> 86).
+constexpr int EDGE_TX = 16;
+struct MarchGeom {
+  int ix, rows;         // strips, rows of the inner rectangle (0: the lattice is too small)
+  int across, up;       // edge tiles per row and per column
+  __host__ __device__ inline MarchGeom(int nx, int ny, int ty, int rx = TL_TX) {
+    const bool ok = nx >= 2 * EDGE_TX + TL_TX && ny >= 6 * ty;
+    ix = ok ? (nx - EDGE_TX + TL_TX - 1) / TL_TX : 0;
+    rows = ok ? ny - 2 * ty : 0;
+    across = (nx + rx - 1) / rx;
+    up = ok ? (rows + 4 * ty - 1) / (4 * ty) : 0;
+  }
+  __host__ __device__ inline int ring() const { return 2 * (across + up); }
+};
+
+// Columns of the tiles along the bottom and top: 64, but 32 on the learned closure, whose four waves run
+// the network on 16 nodes each: a level of 64 and its margin took them two passes.
+template <bool CL>
+constexpr int ring_row_tx() {
+  return CL ? 32 : TL_TX;
+}
+// Edge tile b of a march; the block of a number past the last leaves.
+template <int S, int TY, int NT, bool NTS, int CM, bool CL>
+__device__ __attribute__((always_inline)) inline void march_ring_tile(const LatDesc& L, int parity, int b,
+                                                                      const MarchGeom& m) {
+  constexpr int RX = ring_row_tx<CL>();
+  const int nx = L.nx, ny = L.ny;
+  if (b < 2 * m.across) {
+    const int top = b >= m.across, xo = RX * (top ? b - m.across : b), y0 = top ? ny - TY : 0;
+    three_step_tile_at<S, RX, TY, TY, NT, NTS, CM, CL>(L, parity, min(xo, nx - RX), y0, xo, y0, 2);
+  } else if (b < m.ring()) {
+    const int e = b - 2 * m.across, x0 = (e & 1) ? nx - EDGE_TX : 0, yo = TY + 4 * TY * (e >> 1);
+    three_step_tile_at<S, EDGE_TX, 4 * TY, TY, NT, NTS, CM, CL>(L, parity, x0, min(yo, ny - 5 * TY), x0, yo, 2);
+  }
+}
+
 // The march items of a launch part (strip sx of ix, chunk c of chunks):
-// part 0 all of them, part 1 those whose neighbours are all march items
-// (1 <= sx <= ix - 2 and 1 <= c <= chunks - 2: a level-t read or a write of
-// theirs stays 3 nodes or more from every edge tile), part 2 the others (the
-// border of the rectangle).  Part 1 is chunk-major; part 2 is row c = 0, then
-// the two ends of each middle row, then row chunks - 1.  Block m takes item
-// (m mod 8) * per + m / 8 of its part, so each XCD works through a
-// contiguous stretch; false past the part's last item.
-__host__ __device__ inline int march_part_items(int ix, int chunks, int part) {
-  const int inner = ix > 2 && chunks > 2 ? (ix - 2) * (chunks - 2) : 0;
+// part 0 all of them, part 1 those whose level-t reads and writes stay 3 nodes or
+// more from every edge tile (1 <= sx <= ix - 1 - rb and 1 <= c <= chunks - 2),
+// part 2 the others (the border of the rectangle).  rb: border strips on the right,
+// 2 where the last strip is moved back, else 1.  Part 1 is chunk-major; part 2 is row
+// c = 0, then the ends of each middle row, then row chunks - 1.  In each run of 64
+// blocks XCD k (blocks m = k mod 8) takes 8 consecutive items: neighbouring strips
+// mostly share an L2, and the eight XCDs stream through the same rows.  With an
+// eighth of the list each they had eight regions open in memory (4096^2 us per step,
+// FP32 84.6 -> 83.1, with loads two rounds ahead 85.2 -> 80.4; FP64 172.7 -> 167.3; 4 or 16
+// items are within 1 %, 1 is 10 % slower).
+constexpr int MARCH_RUN = 8;
+__host__ __device__ inline int march_part_items(int ix, int chunks, int part, int rb = 1) {
+  const int fx = ix - 1 - rb, fc = chunks - 2;
+  const int inner = fx > 0 && fc > 0 ? fx * fc : 0;
   return part == 0 ? ix * chunks : (part == 1 ? inner : ix * chunks - inner);
 }
-__host__ __device__ inline bool march_item(int m, int ix, int chunks, int part, int& c, int& sx) {
-  const int items = march_part_items(ix, chunks, part), per = (items + 7) >> 3;
-  const int item = (m & 7) * per + (m >> 3);
+__host__ __device__ inline int march_blocks(int items) {
+  return (items + 8 * MARCH_RUN - 1) / (8 * MARCH_RUN) * (8 * MARCH_RUN);
+}
+__host__ __device__ inline bool march_item(int m, int ix, int chunks, int part, int& c, int& sx, int rb = 1) {
+  const int items = march_part_items(ix, chunks, part, rb);
+  const int item = (m & ~(8 * MARCH_RUN - 1)) + (m & 7) * MARCH_RUN + ((m >> 3) & (MARCH_RUN - 1));
   if (item >= items) return false;
-  const int fx = ix - 2, fc = chunks - 2;
+  const int fx = ix - 1 - rb, fc = chunks - 2;
   if (part == 1) {
     c = 1 + item / fx;
     sx = 1 + item % fx;
@@ -128,13 +182,14 @@ __host__ __device__ inline bool march_item(int m, int ix, int chunks, int part, 
   } else if (item < ix) {
     c = 0;
     sx = item;
-  } else if (item < ix + 2 * fc) {
+  } else if (item < ix + (1 + rb) * fc) {
     const int k = item - ix;
-    c = 1 + (k >> 1);
-    sx = (k & 1) ? ix - 1 : 0;
+    c = 1 + k / (1 + rb);
+    const int j = k % (1 + rb);
+    sx = j == 0 ? 0 : ix - 1 - rb + j;
   } else {
     c = chunks - 1;
-    sx = item - ix - 2 * fc;
+    sx = item - ix - (1 + rb) * fc;
   }
   return true;
 }
@@ -175,7 +230,7 @@ inline hipError_t launch_three_t(const LatDesc& L, int parity, hipStream_t s, in
   } else {
     const int tiles_x = (L.nx + TL_TX - 1) / TL_TX, tiles_y = (L.ny + TY - 1) / TY;
     const int n = CL ? tiles_x * tiles_y - inner_cols(L.nx) * inner_rows(L.ny, TY)
-                     : (part >= 3 ? (march_part_items(inner_cols(L.nx), inner_rows(L.ny, TY), part - 2) + 7) >> 3 << 3
+                     : (part >= 3 ? march_blocks(march_part_items(inner_cols(L.nx), inner_rows(L.ny, TY), part - 2))
                                   : ((tiles_x * tiles_y + 7) >> 3) * 8);
     if (n == 0) return hipSuccess;
     const dim3 grid(n);
@@ -201,6 +256,25 @@ inline hipError_t launch_three_s(const LatDesc& L, int parity, int id, hipStream
   LBM_THREE_STEP(X)
 #undef X
   return hipErrorInvalidValue;
+}
+
+// The edge tiles of a closure lattice's march, one block each.
+template <int S, int TY, int CM>
+__global__ __launch_bounds__(CL_THREADS, (three_step_waves<S, true>())) void k_march_ring(LatDesc L, int parity) {
+  march_ring_tile<S, TY, CL_THREADS, true, CM, true>(L, parity, blockIdx.x, MarchGeom(L.nx, L.ny, TY, ring_row_tx<true>()));
+}
+template <int S, int TY>
+inline hipError_t launch_march_ring_t(const LatDesc& L, int parity, hipStream_t s) {
+  if constexpr (!three_step_fits_closure<S, TY>()) {
+    return hipErrorInvalidValue;
+  } else {
+    const dim3 grid(MarchGeom(L.nx, L.ny, TY, ring_row_tx<true>()).ring());
+    if (L.coll == COLL_MRT)
+      k_march_ring<S, TY, COLL_MRT><<<grid, dim3(CL_THREADS), 0, s>>>(L, parity);
+    else
+      k_march_ring<S, TY, COLL_BGK><<<grid, dim3(CL_THREADS), 0, s>>>(L, parity);
+    return hipGetLastError();
+  }
 }
 
 // Whether three-step shape `id` fits the LDS in storage format `store`, with
@@ -236,11 +310,11 @@ inline bool three_step_fits_store(int store, int id, bool closure) {
   return false;
 }
 
-// Chunk rows of a march over an inner rectangle of `rows` rows in chunks of
-// about h: the count, and the height of all but the last.
-__host__ __device__ inline void march_chunks(int rows, int h, int& chunks, int& height) {
-  chunks = rows > 0 ? (rows + h - 1) / h : 0;
-  height = chunks > 0 ? (rows + chunks - 1) / chunks : 0;
+// Chunks of a march over `rows` rows in chunks of about h; chunk c is rows c
+// rows / chunks .. (c + 1) rows / chunks - 1 of them (no chunk is short).
+__host__ __device__ inline int march_chunks(int rows, int h) { return (rows + h - 1) / h; }
+__host__ __device__ inline int march_row(int c, int rows, int chunks) {
+  return (int)((int64_t)c * rows / chunks);
 }
 
 // Column march (TY: the level arrays' tile rows): the block owns the 64
@@ -264,8 +338,6 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
   using R = typename C::R;
   constexpr int RR = MR + 2;
   constexpr int NI = (MR * T3_W1 + NT - 1) / NT;
-  auto& r1 = three_lds1<S, TY>();
-  auto& r2 = three_lds2<S, TY>();
   const int tid = threadIdx.x;
   const T* __restrict__ A = static_cast<const T*>(buf_of(Ld, parity));
   T* __restrict__ B = static_cast<T*>(buf_of(Ld, parity ^ 1));
@@ -292,8 +364,8 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
   };
   // LDS as element offsets from the arrays' first element (32-bit
   // arithmetic; population i's plane of a level array at a constant offset)
-  T* const l1 = &r1[0][0][0];
-  T* const l2 = &r2[0][0][0];
+  T* const l1 = three_lds1<S, TY>();
+  T* const l2 = three_lds2<S, TY>();
   constexpr int P1 = (TY + 4) * T3_W1, P2 = (TY + 2) * T3_W2;
   const OutPlanes<T> out(B, plane);
   // ring slot of a row: su (the round's first row's slot, uniform) + r, wrapped once
@@ -403,51 +475,44 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
   }
 }
 
-// Blocks below ring8 take the edge tiles (ring_tile order, padded to a
-// multiple of 8), the others the strips' chunks in XCD bands: XCD k takes
-// the k-th contiguous eighth of the chunk-major list, so neighbouring strips
-// share its L2.  The edge tiles come first: they are the slower blocks.
+// Blocks below ring8 take the edge tiles (march_ring_tile, padded to a multiple
+// of 8), the others the strips' chunks (march_item).  The edge tiles come first:
+// they are the slower blocks.
 template <int S, int TY, int MR, int NT, bool NTS, int CM, int PF>
-__global__ __launch_bounds__(NT, two_step_waves<S>()) void k_three_march(LatDesc L, int parity, int tiles_x,
-                                                                       int tiles_y, int ring8, int height,
-                                                                       int chunks, int part) {
-  const int ix = inner_cols(L.nx), iy = inner_rows(L.ny, TY);
+__global__ __launch_bounds__(NT, two_step_waves<S>()) void k_three_march(LatDesc L, int parity, int ring8, int chunks,
+                                                                       int part) {
+  const MarchGeom g(L.nx, L.ny, TY);
   const int b = blockIdx.x;
   if (b < ring8) {
-    int txi, tyi;
-    if (!ring_tile(b, tiles_x, tiles_y, ix, iy, txi, tyi)) return;  // padding: the block leaves before any barrier
-    three_step_tile<S, TY, NT, NTS, CM, false>(L, parity, txi, tyi, 2);
+    march_ring_tile<S, TY, NT, NTS, CM, false>(L, parity, b, g);
     return;
   }
   // (ring8 is a multiple of 8, so m and b run on the same XCD)
   int c, sx;
-  if (!march_item(b - ring8, ix, chunks, part, c, sx)) return;
-  const int ya = TY + c * height, yb = min(ya + height, TY * (iy + 1));
-  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, TL_TX * (1 + sx), ya, yb);
+  if (!march_item(b - ring8, g.ix, chunks, part, c, sx, 2)) return;
+  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, min(max(TL_TX * sx, EDGE_TX), L.nx - EDGE_TX - TL_TX),
+                                               TY + march_row(c, g.rows, chunks), TY + march_row(c + 1, g.rows, chunks));
 }
 
 // One launch: the edge tiles (unless !ring: a closure lattice's run in the
 // closure kernel) and part `part` of the march over the inner rectangle in
-// chunks of about h rows (march_item).
+// chunks of about h rows (march_item), on a lattice that march_fits.
+inline bool march_fits(const LatDesc& L, int ty) { return MarchGeom(L.nx, L.ny, ty).ix > 0; }
 template <int S, int TY, int MR, int NT, bool NTS, int PF>
 inline hipError_t launch_march_t(const LatDesc& L, int parity, hipStream_t s, int h, bool ring, int part) {
   if constexpr (!three_step_fits<S, TY>()) {
     return hipErrorInvalidValue;
   } else {
-    const int tiles_x = (L.nx + TL_TX - 1) / TL_TX, tiles_y = (L.ny + TY - 1) / TY;
-    const int ix = inner_cols(L.nx), iy = inner_rows(L.ny, TY);
-    const int ring8 = ring ? (tiles_x * tiles_y - ix * iy + 7) / 8 * 8 : 0;
-    int chunks, height;
-    march_chunks(ix > 0 ? TY * iy : 0, h, chunks, height);
-    const int items = march_part_items(ix, chunks, part);
+    const MarchGeom g(L.nx, L.ny, TY);
+    if (g.ix == 0) return hipErrorInvalidValue;
+    const int ring8 = ring ? (g.ring() + 7) / 8 * 8 : 0, chunks = march_chunks(g.rows, h);
+    const int items = march_part_items(g.ix, chunks, part, 2);
     if (ring8 + items == 0) return hipSuccess;
-    const dim3 grid(ring8 + (items + 7) / 8 * 8);
+    const dim3 grid(ring8 + march_blocks(items));
     if (L.coll == COLL_MRT)
-      k_three_march<S, TY, MR, NT, NTS, COLL_MRT, PF>
-          <<<grid, dim3(NT), 0, s>>>(L, parity, tiles_x, tiles_y, ring8, height, chunks, part);
+      k_three_march<S, TY, MR, NT, NTS, COLL_MRT, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part);
     else
-      k_three_march<S, TY, MR, NT, NTS, COLL_BGK, PF>
-          <<<grid, dim3(NT), 0, s>>>(L, parity, tiles_x, tiles_y, ring8, height, chunks, part);
+      k_three_march<S, TY, MR, NT, NTS, COLL_BGK, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part);
     return hipGetLastError();
   }
 }
@@ -607,8 +672,7 @@ inline hipError_t launch_two_march_t(const LatDesc& L, int parity, hipStream_t s
   const int tiles_x = (L.nx + TL_TX - 1) / TL_TX, tiles_y = (L.ny + TY - 1) / TY;
   const int ix = inner_cols(L.nx), iy = inner_rows2(L.ny, TY);
   const int ring8 = (tiles_x * tiles_y - ix * iy + 7) / 8 * 8;
-  int chunks, height;
-  march_chunks(ix > 0 ? TY * iy : 0, h, chunks, height);
+  const int chunks = march_chunks(ix > 0 ? TY * iy : 0, h), height = chunks > 0 ? (TY * iy + chunks - 1) / chunks : 0;
   const dim3 grid(ring8 + (ix * chunks + 7) / 8 * 8);
   if (L.coll == COLL_MRT)
     k_two_march<S, TY, MR, NT, NTS, COLL_MRT><<<grid, dim3(NT), 0, s>>>(L, parity, tiles_x, tiles_y, ring8, height, chunks);
@@ -622,5 +686,6 @@ hipError_t launch_two_march(const LatDesc& L, int parity, int id, hipStream_t s)
 
 // three-step launch of a lattice with the learned closure (lbm_twostep_cl.hip)
 hipError_t launch_three_step_closure(const LatDesc& L, int parity, int id, hipStream_t s);
+hipError_t launch_march_ring_closure(const LatDesc& L, int parity, int ty, hipStream_t s);
 
 }  // namespace lbm

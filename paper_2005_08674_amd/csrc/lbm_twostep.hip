@@ -193,84 +193,69 @@ bool three_step_supported(const LatDesc& L, int id) {
          three_step_fits_store(L.store, id, L.closure && L.net);
 }
 
-// The tile shape whose edge tiles a march shape's closure lattice runs in
-// the closure kernel: the first tile shape with the march's tile rows.
-static int closure_tile_of(int id) {
+// The first tile shape with a march shape's tile rows: it runs the march's edge
+// tiles of a closure lattice, and the whole of a lattice too small for the march.
+static int tile_shape_of(int id) {
   for (int k = 0; k < kNumThree; ++k)
     if (kThree[k].mr == 0 && kThree[k].ty == kThree[id].ty) return k;
   return -1;
 }
 
 // One launch of a tile or march shape, except on the learned closure, which
-// takes two: its edge tiles with the network and its inner tiles (tile
-// shapes) or inner strips (march shapes) with the plain sweep (both read
-// buffer `parity` and write disjoint parts of the other).  With a second stream
-// `side` the edge-tile kernel runs there, forked from `s` after the work
-// already on it (event `fork`) and joined back before what follows (event
-// `join`), so the two kernels share the GPU; without one they run in turn
-// on `s`.
-// A closure launch on two streams: the edge-tile kernel on `side` after
-// everything already on s (the fork), the inner part on s.  Launch n's
-// edge-tile kernel needs launch n - 1's inner part done (it reads that
-// part's output and overwrites the buffer that part read) and launch n's
-// inner part needs launch n - 1's edge-tile kernel done (the same, the other
-// way); with kJoinDefer on every launch but the last and kJoinPrev on every
-// launch but the first, those are the only waits, so the edge-tile kernels,
-// the longer of the two, follow one another on `side` without a round trip
-// through s.  The inner part splits further: its march items or inner tiles
-// away from the edge tiles depend on neither edge-tile kernel and run before
-// the wait.
+// takes its edge tiles with the network in a kernel of their own (both kernels read
+// buffer `parity` and write disjoint parts of the other one).  With a second stream
+// `side` that kernel runs there, forked from `s` after the work already on it
+// (event `fork`) and joined back before what follows (event `join`); without one
+// the kernels run in turn on `s`.
+//
+// The inner part splits in two: its border (the march items or inner tiles that
+// share values with an edge tile) and its middle, which stays 3 nodes or more from
+// every edge tile.  Launch n's edge tiles need launch n - 1's border and edge tiles,
+// launch n's border needs launch n - 1's edge tiles, border and middle, and launch
+// n's middle only what ran on s before it.  So s runs each launch's border first and
+// records `fork` there: the edge tiles of the next launch run beside this launch's
+// middle and need to end only before that launch's border is through (with kJoinDefer
+// on every launch but the last and kJoinPrev on every launch but the first).  With the
+// middle first, the edge tiles started after it and the next border waited for them.
+// 2048^2 FP32 on the vortex, most side tiles through the regime gate: 128 -> 103 us per
+// launch together with the narrower edge tiles and the weights in registers (one
+// fork and join per launch, border and middle in one kernel: 109 to 121).
 hipError_t launch_three_step(const LatDesc& L, int parity, int id, hipStream_t s, hipStream_t side, hipEvent_t fork,
                              hipEvent_t join, int flags) {
   if (!three_step_supported(L, id)) return hipErrorInvalidValue;
-  const bool march = kThree[id].mr > 0;
+  if (kThree[id].mr > 0 && !march_fits(L, kThree[id].ty)) id = tile_shape_of(id);
+  const bool closure = L.closure && L.net, march = kThree[id].mr > 0;
   const int mid = id - (kNumThree - kNumMarch);
-  if (march && !(L.closure && L.net)) return launch_three_march(L, parity, mid, s, true);
-  int part = 0;
-  const bool forked = L.closure && L.net && side && fork && join;
-  if (L.closure && L.net) {
-    hipError_t e = hipSuccess;
-    if (forked) {
-      e = hipEventRecord(fork, s);
-      if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
+  // part 0: all, 1: without the edge tiles, 3: the inner part's middle, 4: its border
+  auto inner = [&](int part) {
+    if (march) return launch_three_march(L, parity, mid, s, part == 0, part >= 3 ? part - 2 : 0);
+    switch (L.store) {
+      case ST_F64: return launch_three_s<ST_F64, false>(L, parity, id, s, part);
+      case ST_F32: return launch_three_s<ST_F32, false>(L, parity, id, s, part);
+      case ST_F16: return launch_three_s<ST_F16, false>(L, parity, id, s, part);
+      case ST_BF16: return launch_three_s<ST_BF16, false>(L, parity, id, s, part);
     }
-    const int cid = march ? closure_tile_of(id) : id;
-    if (e == hipSuccess) e = cid >= 0 ? launch_three_step_closure(L, parity, cid, forked ? side : s) : hipErrorInvalidValue;
-    // the march items (inner tiles) whose reads and writes stay 3 nodes or
-    // more from every edge tile touch nothing an edge-tile kernel reads or
-    // writes: they go before the wait for the previous launch's edge-tile
-    // kernel
-    if (forked && march && e == hipSuccess) e = launch_three_march(L, parity, mid, s, false, 1);
-    if (forked && !march && e == hipSuccess) {
-      switch (L.store) {
-        case ST_F64: e = launch_three_s<ST_F64, false>(L, parity, id, s, 3); break;
-        case ST_F32: e = launch_three_s<ST_F32, false>(L, parity, id, s, 3); break;
-        case ST_F16: e = launch_three_s<ST_F16, false>(L, parity, id, s, 3); break;
-        case ST_BF16: e = launch_three_s<ST_BF16, false>(L, parity, id, s, 3); break;
-      }
-    }
-    // s waits for the previous launch's edge-tile kernel before join is recorded anew
-    if (forked && (flags & kJoinPrev) && e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
-    if (forked && e == hipSuccess) e = hipEventRecord(join, side);
-    if (e != hipSuccess) return e;
-    part = forked ? 4 : 1;
+    return hipErrorInvalidValue;
+  };
+  auto edges = [&](hipStream_t es) {
+    return march ? launch_march_ring_closure(L, parity, kThree[id].ty, es) : launch_three_step_closure(L, parity, id, es);
+  };
+  if (!closure) return inner(0);
+  if (!(side && fork && join)) {
+    const hipError_t e = edges(s);
+    return e == hipSuccess ? inner(1) : e;
   }
-  const bool wait_end = forked && !(flags & kJoinDefer);
-  hipError_t e = hipErrorInvalidValue;
-  if (march) {
-    // the closure kernel took the edge tiles: the march covers the inner
-    // rectangle (on two streams, the items bordering the edge tiles here)
-    e = launch_three_march(L, parity, mid, s, false, forked ? 2 : 0);
-    if (wait_end && e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
-    return e;
-  }
-  switch (L.store) {
-    case ST_F64: e = launch_three_s<ST_F64, false>(L, parity, id, s, part); break;
-    case ST_F32: e = launch_three_s<ST_F32, false>(L, parity, id, s, part); break;
-    case ST_F16: e = launch_three_s<ST_F16, false>(L, parity, id, s, part); break;
-    case ST_BF16: e = launch_three_s<ST_BF16, false>(L, parity, id, s, part); break;
-  }
-  if (wait_end && e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
+  hipError_t e = hipSuccess;
+  if (!(flags & kJoinPrev)) e = hipEventRecord(fork, s);
+  if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
+  if (e == hipSuccess) e = edges(side);
+  // s waits for the previous launch's edge tiles before join is recorded anew
+  if ((flags & kJoinPrev) && e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
+  if (e == hipSuccess) e = hipEventRecord(join, side);
+  if (e == hipSuccess) e = inner(4);
+  if ((flags & kJoinDefer) && e == hipSuccess) e = hipEventRecord(fork, s);
+  if (e == hipSuccess) e = inner(3);
+  if (!(flags & kJoinDefer) && e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
   return e;
 }
 

@@ -17,4 +17,21 @@ hipError_t launch_three_step_closure(const LatDesc& L, int parity, int id, hipSt
   return hipErrorInvalidValue;
 }
 
+// Edge tiles of a march of `ty` tile rows (8 or 12, the rows of LBM_THREE_MARCH).
+template <int S>
+static hipError_t launch_march_ring_s(const LatDesc& L, int parity, int ty, hipStream_t s) {
+  if (ty == 8) return launch_march_ring_t<S, 8>(L, parity, s);
+  if (ty == 12) return launch_march_ring_t<S, 12>(L, parity, s);
+  return hipErrorInvalidValue;
+}
+hipError_t launch_march_ring_closure(const LatDesc& L, int parity, int ty, hipStream_t s) {
+  switch (L.store) {
+    case ST_F64: return launch_march_ring_s<ST_F64>(L, parity, ty, s);
+    case ST_F32: return launch_march_ring_s<ST_F32>(L, parity, ty, s);
+    case ST_F16: return launch_march_ring_s<ST_F16>(L, parity, ty, s);
+    case ST_BF16: return launch_march_ring_s<ST_BF16>(L, parity, ty, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace lbm

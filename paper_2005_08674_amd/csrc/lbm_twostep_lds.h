@@ -310,16 +310,17 @@ __host__ __device__ constexpr int light_waves_start(int n, int nt) {
   return n % nt == 0 ? 0 : ((n % nt + 63) / 64 * 64) % nt;
 }
 
-// The two level arrays of a three-step block, one allocation per kernel
-// whichever path (tile or column march) takes them.
+// The two level arrays of a three-step block of TY tile rows (64 columns), one
+// allocation per kernel whichever path takes them (64-column tile, edge column
+// tile or column march), each viewed as its own [9][rows][columns].
 template <int S, int TY>
-__device__ inline auto three_lds1() -> typename Codec<S>::T (&)[9][TY + 4][T3_W1] {
-  __shared__ __attribute__((aligned(16))) typename Codec<S>::T a[9][TY + 4][T3_W1];
+__device__ inline typename Codec<S>::T* three_lds1() {
+  __shared__ __attribute__((aligned(16))) typename Codec<S>::T a[9 * (TY + 4) * T3_W1];
   return a;
 }
 template <int S, int TY>
-__device__ inline auto three_lds2() -> typename Codec<S>::T (&)[9][TY + 2][T3_W2] {
-  __shared__ __attribute__((aligned(16))) typename Codec<S>::T a[9][TY + 2][T3_W2];
+__device__ inline typename Codec<S>::T* three_lds2() {
+  __shared__ __attribute__((aligned(16))) typename Codec<S>::T a[9 * (TY + 2) * T3_W2];
   return a;
 }
 
@@ -396,12 +397,11 @@ __device__ inline void tl_edge_count(int nx, int ny, int rx0, int ry0, int rw, i
 // loop, so it is kept compact (one copy for the three levels, loops rolled):
 // its instructions come from L2 on every tile, and their count, not the
 // arithmetic, sets its time.
-template <int S, int CLW>
+template <int S, int CLW, class PopsFn>
 __device__ inline __attribute__((always_inline)) void closure_level(const LatDesc& Ld, int rx0, int ry0, int rw, int rh,
-                                           const typename Codec<S>::T* prev, int64_t ps_i, int ps_y, int ox, int oy,
-                                           char* scr, float* cl_y, int nt, const mlp::Params& par) {
-  using C = Codec<S>;
-  using R = typename C::R;
+                                                                    PopsFn pops, char* scr, float* cl_y, int nt,
+                                                                    const mlp::Params& par, const mlp::Frags& weights) {
+  using R = typename Codec<S>::R;
   const int nx = Ld.nx, ny = Ld.ny;
   const int tid = threadIdx.x;
   const mlp::Net& net = *static_cast<const mlp::Net*>(Ld.net);
@@ -409,11 +409,6 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
   const R rho0 = R(Ld.rho0);
   const R ref[3] = {R(Ld.m0[0]), R(Ld.m0[1]), R(Ld.m0[2])};
   const float rho0f = float(Ld.rho0), omegaf = float(Ld.omega);
-  auto pops = [&](int x, int y, R g[9]) {
-    const int64_t idx = (int64_t)(y - oy) * ps_y + (x - ox);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) g[i] = C::dec(prev[i * ps_i + idx], Ld.ds[i]);
-  };
   int xl, xh, yl, yh, ncol, nrow;
   tl_edge_count(nx, ny, rx0, ry0, rw, rh, xl, xh, yl, yh, ncol, nrow);
   const int left = xl == 0, right = xh == nx - 1, hcol = yh - yl + 1;
@@ -471,15 +466,15 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
         float A = 0.f, inv = 0.f;
         bool gated = false;
         if (eligible) {
-          A = strip_amplitude(fv, rho0f);
+          A = strip_amplitude<1>(fv, rho0f);
           inv = amplitude_inverse(A);
           auto scaled = [&](int jj, int q) { return fv(jj, q) * inv; };
-          gated = vortical_row(scaled, rho0f, net.kmin);
+          gated = vortical_row<1>(scaled, rho0f, net.kmin);
         }
         if (c == 0 && valid) cl_y[4 * (base_e + i) + 3] = gated ? A : 0.f;
         if (__ballot(gated) == 0) continue;              // wave-uniform
         float dmc[3] = {0.f, 0.f, 0.f}, refn[3] = {0.f, 0.f, 0.f};
-        if (eligible) {
+        if (eligible && c == 1) {
           // inputs 82..86: m_c - m0 and m0 in the edge frame
           int x, y;
           strip_xy(0, tc, x, y);
@@ -492,23 +487,35 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
           normal_frame_diff<R>(mc.v, ref, enx, eny, dmc);
           to_normal_frame<R>(ref, b, enx, eny, refn);
         }
+        // inputs 9 jj .. 9 jj + 8 for jj = c, c + 4, c + 8: strip node jj up to 8, the other six
+        // inputs and the zeros past them at jj = 9 and 10
+        static_assert(F_STRIP == 9 * NODE_FEAT && NODE_FEAT == 9 && F_OMEGA == 81 && F_MC == 82 && F_UREF == 85, "rows");
         mlp::bf16* row = X + r * mlp::XS;
-#pragma unroll 4
-        for (int qq = 0; qq < mlp::IN / 4; ++qq) {
-          const int q = 4 * qq + c;
-          // input_value(q, ...) with the choice made by selects
-          const int qs = min(q, F_STRIP - 1);
-          const float strip = fv(qs / NODE_FEAT, qs % NODE_FEAT) * inv;
-          const int m = min(max(q - F_MC, 0), 2), u = min(max(q - F_UREF, 0), 1);
-          const float dm = (m == 0 ? dmc[0] : (m == 1 ? dmc[1] : dmc[2])) * inv;
-          const float ur = u == 0 ? refn[1] : refn[2];
-          const float v = q < F_STRIP ? strip : (q == F_OMEGA ? omegaf : (q < F_UREF ? dm : (q < mlp::NFEAT ? ur : 0.f)));
-          row[q] = eligible ? normalised_input(par.mean, par.inv_std, q, v) : (mlp::bf16)0.f;
+#pragma unroll 1
+        for (int t = 0; t < 3; ++t) {
+          const int jj = c + 4 * t;
+          float v[NODE_FEAT];
+#pragma unroll
+          for (int q = 0; q < NODE_FEAT; ++q) v[q] = fv(min(jj, 8), q) * inv;
+          if (jj > 8) {
+            const bool tail = jj == 9;
+            v[0] = tail ? omegaf : 0.f;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) v[1 + q] = tail ? dmc[q] * inv : 0.f;
+            v[4] = tail ? refn[1] : 0.f;
+            v[5] = tail ? refn[2] : 0.f;
+            v[6] = v[7] = v[8] = 0.f;
+          }
+#pragma unroll
+          for (int q = 0; q < NODE_FEAT; ++q) {
+            const int k = NODE_FEAT * jj + q;
+            if (k < mlp::IN) row[k] = eligible ? normalised_input(par.mean, par.inv_std, k, v[q]) : (mlp::bf16)0.f;
+          }
         }
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_s_waitcnt(0);
         mlp::f32x4 yv;
-        mlp::forward16(par, X, H1, X, yv);
+        mlp::forward16(weights, par, X, H1, X, yv);
         const int col = l & 15;
         if (col < 3) {
 #pragma unroll
@@ -525,30 +532,49 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
   }
 }
 
+// The closure's LDS (scratch of its own where the level arrays have no room for
+// it, outputs and amplitudes per edge node, network parameters), one
+// allocation per kernel like the level arrays.
+template <int S, int TY, int NT, bool OWN>
+__device__ inline char* cl_lds_own() {
+  __shared__ __attribute__((aligned(16))) char a[OWN ? CL_FEAT_BYTES + cl_waves<S, TY, NT>() * CL_WAVE_BYTES : 16];
+  return a;
+}
+template <int TY, bool CL>
+__device__ inline float (*cl_lds_y())[4] {
+  __shared__ float a[CL ? cl_max_edge<TY>() : 1][4];
+  return a;
+}
+template <bool CL>
+__device__ inline char* cl_lds_par() {
+  __shared__ __attribute__((aligned(16))) char a[CL ? mlp::PARAM_BYTES : 16];
+  return a;
+}
+
+// One TX x TY tile at (x0, y0), three steps; its block stores the nodes at or
+// beyond (xo, yo).  LY: the tile rows the level arrays are sized for (64 columns).
 // `part` selects the tiles a launch updates: 0 every tile, 1 the inner tiles
 // only, 2 the edge tiles only (a tile of the other kind returns before any
 // barrier); a lattice on the learned closure runs its edge tiles with CL in
 // one launch and its inner tiles without in another.
-// part: 0 the tile, 1 only an inner tile, 2 only an edge tile.
-template <int S, int TY, int NT, bool NTS, int CM, bool CL = false>
-__device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, int tyi, int part = 0) {
+template <int S, int TX, int TY, int LY, int NT, bool NTS, int CM, bool CL = false>
+__device__ __attribute__((always_inline)) inline void three_step_tile_at(const LatDesc& Ld, int parity, int x0, int y0, int xo, int yo, int part) {
   using C = Codec<S>;
   using T = typename C::T;
   using R = typename C::R;
-  auto& lds1 = three_lds1<S, TY>();
-  auto& lds2 = three_lds2<S, TY>();
-  constexpr int CLW = cl_waves<S, TY, NT>();
-  constexpr bool CL_OWN = CL && cl_own_lds<S, TY, NT>();
-  __shared__ __attribute__((aligned(16))) char cl_own[CL_OWN ? CL_FEAT_BYTES + CLW * CL_WAVE_BYTES : 16];
-  __shared__ float cl_y[CL ? cl_max_edge<TY>() : 1][4];
-  __shared__ __attribute__((aligned(16))) char cl_par[CL ? mlp::PARAM_BYTES : 16];
+  constexpr int W1 = TX + 4, W2 = TX + 2;
+  static_assert((TY + 4) * W1 <= (LY + 4) * T3_W1 && (TY + 2) * W2 <= (LY + 2) * T3_W2, "tile exceeds the level arrays");
+  static_assert(2 * (TY + 4) + 2 * W1 <= cl_max_edge<LY>() && TY + 6 <= CL_STRIP, "tile exceeds the closure's arrays");
+  auto& lds1 = *reinterpret_cast<T(*)[9][TY + 4][W1]>(three_lds1<S, LY>());
+  auto& lds2 = *reinterpret_cast<T(*)[9][TY + 2][W2]>(three_lds2<S, LY>());
+  constexpr int CLW = cl_waves<S, LY, NT>();
+  constexpr bool CL_OWN = CL && cl_own_lds<S, LY, NT>();
+  char* const cl_own = cl_lds_own<S, LY, NT, CL_OWN>();
+  float(*const cl_y)[4] = cl_lds_y<LY, CL>();
+  char* const cl_par = cl_lds_par<CL>();
 
   const int nx = Ld.nx, ny = Ld.ny;
-  const int x0 = min(txi * TL_TX, nx - TL_TX), y0 = min(tyi * TY, ny - TY);
-  // a last tile moved back to end at the lattice edge stores only the nodes
-  // its neighbour does not (the overlap holds the same values in both)
-  const int xo = txi * TL_TX, yo = tyi * TY;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
   const T* __restrict__ A = static_cast<const T*>(buf_of(Ld, parity));
   T* __restrict__ B = static_cast<T*>(buf_of(Ld, parity ^ 1));
   const int pitch = Ld.pitch;
@@ -558,7 +584,7 @@ __device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, i
 
   // Inner tile: every level t + 1 node and its pull sources lie inside the
   // lattice and away from its edges: no clamps, no NSBC.
-  const bool inner = x0 >= 3 && x0 + TL_TX + 3 <= nx && y0 >= 3 && y0 + TY + 3 <= ny;
+  const bool inner = x0 >= 3 && x0 + TX + 3 <= nx && y0 >= 3 && y0 + TY + 3 <= ny;
   if ((part == 1 && !inner) || (part == 2 && inner)) return;
   auto interior_node = [&](int x, int y) { return x >= 1 && x <= nx - 2 && y >= 1 && y <= ny - 2; };
 
@@ -570,12 +596,12 @@ __device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, i
   // same unconditional loads, as in an inner tile.
   auto level1 = [&](const Base<R>& b, auto edge) __attribute__((always_inline)) {
     constexpr bool E = decltype(edge)::value;
-    constexpr int N1 = (TY + 4) * T3_W1;
+    constexpr int N1 = (TY + 4) * W1;
 #pragma unroll
     for (int it = 0; it < (N1 + NT - 1) / NT; ++it) {
       const int k = tid + it * NT;
       if (k < N1) {
-        const int r = k / T3_W1, cx = k - r * T3_W1;
+        const int r = k / W1, cx = k - r * W1;
         int x = x0 - 2 + cx, y = y0 - 2 + r;
         bool keep = true;
         if constexpr (E) {
@@ -602,12 +628,12 @@ __device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, i
   // (LDS reads of a dropped node stay inside the arrays; its values are unused.)
   auto level2 = [&](const Base<R>& b, auto edge) __attribute__((always_inline)) {
     constexpr bool E = decltype(edge)::value;
-    constexpr int N2 = (TY + 2) * T3_W2;
+    constexpr int N2 = (TY + 2) * W2;
 #pragma unroll
     for (int it = 0; it < (N2 + NT - 1) / NT; ++it) {
       const int k = tid + it * NT;
       if (k < N2) {
-        const int r = k / T3_W2, cx = k - r * T3_W2;
+        const int r = k / W2, cx = k - r * W2;
         R g[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i) g[i] = C::raw(lds1[i][r + 1 - kCy[i]][cx + 1 - kCx[i]]);
@@ -633,12 +659,12 @@ __device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, i
   };
   auto level3 = [&](const Base<R>& b, auto edge) __attribute__((always_inline)) {
     constexpr bool E = decltype(edge)::value;
-    constexpr int N3 = TY * TL_TX;
+    constexpr int N3 = TY * TX;
 #pragma unroll
     for (int it = 0; it < (N3 + NT - 1) / NT; ++it) {
       const int k = tid + it * NT;
       if (k < N3) {
-        const int r = k / TL_TX, cx = k - r * TL_TX;
+        const int r = k / TX, cx = k - r * TX;
         R g[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i) g[i] = C::raw(lds2[i][r + 1 - kCy[i]][cx + 1 - kCx[i]]);
@@ -714,118 +740,145 @@ __device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, i
     return mc;
   };
   // the network's parameters in LDS (CL; read after the first closure phase's barrier)
+  // and its weights in registers: read per level and layer they came through an L2 that the march
+  // beside this kernel streams through (2048^2: a level of a side tile past the gate 12.5 -> 8.4 us)
   mlp::Params par{};
+  mlp::Frags weights;
+  if constexpr (CL) mlp::load_frags(*static_cast<const mlp::Net*>(Ld.net), weights);
   if constexpr (CL) par = mlp::stage_params(*static_cast<const mlp::Net*>(Ld.net), cl_par, tid, NT);
-  // the closure phases of a level (CL): region, previous level (base,
-  // strides, origin) and scratch (the level arrays not in use, or LDS of
-  // their own)
-  auto closure = [&](int rx0, int ry0, int rw, int rh, const T* prev, int64_t ps_i, int ps_y, int ox, int oy,
-                     int level) __attribute__((always_inline)) {
+  // the closure phases of level lv (CL): region and previous level, scratch in the level array
+  // not in use, or LDS of its own.  One copy of the code for the three levels.
+  auto closure = [&](int lv) __attribute__((always_inline)) {
     if constexpr (CL) {
       char* scr = CL_OWN ? cl_own
-                         : (level == 3 ? reinterpret_cast<char*>(&lds1[0][0][0]) : reinterpret_cast<char*>(&lds2[0][0][0]));
-      closure_level<S, CLW>(Ld, rx0, ry0, rw, rh, prev, ps_i, ps_y, ox, oy, scr, &cl_y[0][0], NT, par);
+                         : (lv == 3 ? reinterpret_cast<char*>(&lds1[0][0][0]) : reinterpret_cast<char*>(&lds2[0][0][0]));
+      const int m = 3 - lv;  // the region's margin
+      const T* const p = lv == 2 ? &lds1[0][0][0] : &lds2[0][0][0];
+      const int py = lv == 2 ? W1 : W2, pi = lv == 2 ? (TY + 4) * W1 : (TY + 2) * W2, o0 = (m + 1 - y0) * py + m + 1 - x0;
+      auto pops = [&](int x, int y, R g[9]) __attribute__((always_inline)) {
+        if (lv == 1) {
+          const uint32_t off = (uint32_t)(y * pitch + x) * (uint32_t)sizeof(T);
+#pragma unroll
+          for (int i = 0; i < 9; ++i) g[i] = C::dec(ldg(A + i * plane, off), Ld.ds[i]);
+        } else {
+          const int idx = o0 + y * py + x;
+#pragma unroll
+          for (int i = 0; i < 9; ++i) g[i] = C::dec(p[i * pi + idx], Ld.ds[i]);
+        }
+      };
+      closure_level<S, CLW>(Ld, x0 - m, y0 - m, TX + 2 * m, TY + 2 * m, pops, scr, &cl_y[0][0], NT, par, weights);
     }
   };
 
-  // ---- level t + 1 from HBM
-  auto mom0 = [&](int xx, int yy, R m[3]) { tl_moments_global<S>(Ld, A, xx, yy, b, m); };
-  closure(x0 - 2, y0 - 2, T3_W1, TY + 4, A, plane, pitch, 0, 0, 1);
-  level1(b, std::true_type{});
-  {
-    int xl, xh, yl, yh, ncol, nrow;
-    edge_count(x0 - 2, y0 - 2, T3_W1, TY + 4, xl, xh, yl, yh, ncol, nrow);
-    for (int e = edge_lane((TY + 4) * T3_W1); e < ncol + nrow; e += NT) {
-      int x, y;
-      edge_node(e, xl, xh, yl, yh, ncol, x, y);
-      // sources clamped into the lattice (a clamped source is only ever an unknown population's)
-      const uint32_t unknown = tl_unknown(x, y, nx, ny);
-      const int sxs[3] = {min(x + 1, nx - 1), x, max(x - 1, 0)};
-      const uint32_t srow[3] = {(uint32_t)(min(y + 1, ny - 1) * pitch), (uint32_t)(y * pitch),
-                                (uint32_t)(max(y - 1, 0) * pitch)};
-      R g[9];
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        const R v = C::dec(ldg(A + i * plane, (srow[1 + kCy[i]] + (uint32_t)sxs[1 + kCx[i]]) * (uint32_t)sizeof(T)), Ld.ds[i]);
-        g[i] = (unknown >> i) & 1u ? R(0) : v;
-      }
-      nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom0), rho0, b, Ld.corr_mode);
-      collide<R, CM>(Ld, g, rho0, b, omega);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) lds1[i][y - y0 + 2][x - x0 + 2] = C::enc(g[i], Ld.es[i]);
+#pragma unroll (CL ? 1 : 3)
+  for (int lv = 1; lv <= 3; ++lv) {
+    // (the nodes' indices and addresses of the three levels are formed in their level, not
+    // kept in registers across the loop)
+    if constexpr (CL) {
+      asm volatile("" : "+v"(tid));
     }
+    closure(lv);
+    if (lv == 1) {
+      // ---- level t + 1 from HBM
+      auto mom0 = [&](int xx, int yy, R m[3]) { tl_moments_global<S>(Ld, A, xx, yy, b, m); };
+      level1(b, std::true_type{});
+      int xl, xh, yl, yh, ncol, nrow;
+      edge_count(x0 - 2, y0 - 2, W1, TY + 4, xl, xh, yl, yh, ncol, nrow);
+      for (int e = edge_lane((TY + 4) * W1); e < ncol + nrow; e += NT) {
+        int x, y;
+        edge_node(e, xl, xh, yl, yh, ncol, x, y);
+        // sources clamped into the lattice (a clamped source is only ever an unknown population's)
+        const uint32_t unknown = tl_unknown(x, y, nx, ny);
+        const int sxs[3] = {min(x + 1, nx - 1), x, max(x - 1, 0)};
+        const uint32_t srow[3] = {(uint32_t)(min(y + 1, ny - 1) * pitch), (uint32_t)(y * pitch),
+                                  (uint32_t)(max(y - 1, 0) * pitch)};
+        R g[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+          const R v = C::dec(ldg(A + i * plane, (srow[1 + kCy[i]] + (uint32_t)sxs[1 + kCx[i]]) * (uint32_t)sizeof(T)), Ld.ds[i]);
+          g[i] = (unknown >> i) & 1u ? R(0) : v;
+        }
+        nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom0), rho0, b, Ld.corr_mode);
+        collide<R, CM>(Ld, g, rho0, b, omega);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lds1[i][y - y0 + 2][x - x0 + 2] = C::enc(g[i], Ld.es[i]);
+      }
+    } else if (lv == 2) {
+      // ---- level t + 2 from lds1 (lattice node (x, y) at lds1[.][y - y0 + 2][x - x0 + 2])
+      auto pops1 = [&](int xx, int yy, R q[9]) {
+        const int lx = xx - x0 + 2, ly = yy - y0 + 2;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) q[i] = C::dec(lds1[i][ly][lx], Ld.ds[i]);
+      };
+      auto mom1 = [&](int xx, int yy, R m[3]) {
+        R q[9];
+        pops1(xx, yy, q);
+        moments<R>(q, rho0, b, m[0], m[1], m[2]);
+      };
+      level2(b, std::true_type{});
+      int xl, xh, yl, yh, ncol, nrow;
+      edge_count(x0 - 1, y0 - 1, W2, TY + 2, xl, xh, yl, yh, ncol, nrow);
+      for (int e = edge_lane((TY + 2) * W2); e < ncol + nrow; e += NT) {
+        int x, y;
+        edge_node(e, xl, xh, yl, yh, ncol, x, y);
+        const uint32_t unknown = tl_unknown(x, y, nx, ny);
+        const int lxs[3] = {min(x + 1, nx - 1) - x0 + 2, x - x0 + 2, max(x - 1, 0) - x0 + 2};
+        const int lys[3] = {min(y + 1, ny - 1) - y0 + 2, y - y0 + 2, max(y - 1, 0) - y0 + 2};
+        R g[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+          const R v = C::dec(lds1[i][lys[1 + kCy[i]]][lxs[1 + kCx[i]]], Ld.ds[i]);
+          g[i] = (unknown >> i) & 1u ? R(0) : v;
+        }
+        nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom1), rho0, b, Ld.corr_mode);
+        collide<R, CM>(Ld, g, rho0, b, omega);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lds2[i][y - y0 + 1][x - x0 + 1] = C::enc(g[i], Ld.es[i]);
+      }
+    } else {
+      // ---- level t + 3 on the tile from lds2 (lattice node (x, y) at lds2[.][y - y0 + 1][x - x0 + 1])
+      auto pops2 = [&](int xx, int yy, R q[9]) {
+        const int lx = xx - x0 + 1, ly = yy - y0 + 1;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) q[i] = C::dec(lds2[i][ly][lx], Ld.ds[i]);
+      };
+      auto mom2 = [&](int xx, int yy, R m[3]) {
+        R q[9];
+        pops2(xx, yy, q);
+        moments<R>(q, rho0, b, m[0], m[1], m[2]);
+      };
+      level3(b, std::true_type{});
+      int xl, xh, yl, yh, ncol, nrow;
+      edge_count(x0, y0, TX, TY, xl, xh, yl, yh, ncol, nrow);
+      for (int e = edge_lane(TY * TX); e < ncol + nrow; e += NT) {
+        int x, y;
+        edge_node(e, xl, xh, yl, yh, ncol, x, y);
+        const uint32_t unknown = tl_unknown(x, y, nx, ny);
+        const int lxs[3] = {min(x + 1, nx - 1) - x0 + 1, x - x0 + 1, max(x - 1, 0) - x0 + 1};
+        const int lys[3] = {min(y + 1, ny - 1) - y0 + 1, y - y0 + 1, max(y - 1, 0) - y0 + 1};
+        R g[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+          const R v = C::dec(lds2[i][lys[1 + kCy[i]]][lxs[1 + kCx[i]]], Ld.ds[i]);
+          g[i] = (unknown >> i) & 1u ? R(0) : v;
+        }
+        nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom2), rho0, b, Ld.corr_mode);
+        collide<R, CM>(Ld, g, rho0, b, omega);
+        if (x >= xo && y >= yo) store(x, y, g);
+      }
+    }
+    if (lv < 3) __syncthreads();
   }
-  __syncthreads();
+}
 
-  // ---- level t + 2 from lds1 (lattice node (x, y) at lds1[.][y - y0 + 2][x - x0 + 2])
-  {
-    auto pops1 = [&](int xx, int yy, R q[9]) {
-      const int lx = xx - x0 + 2, ly = yy - y0 + 2;
-#pragma unroll
-      for (int i = 0; i < 9; ++i) q[i] = C::dec(lds1[i][ly][lx], Ld.ds[i]);
-    };
-    auto mom1 = [&](int xx, int yy, R m[3]) {
-      R q[9];
-      pops1(xx, yy, q);
-      moments<R>(q, rho0, b, m[0], m[1], m[2]);
-    };
-    closure(x0 - 1, y0 - 1, T3_W2, TY + 2, &lds1[0][0][0], (TY + 4) * T3_W1, T3_W1, x0 - 2, y0 - 2, 2);
-    level2(b, std::true_type{});
-    int xl, xh, yl, yh, ncol, nrow;
-    edge_count(x0 - 1, y0 - 1, T3_W2, TY + 2, xl, xh, yl, yh, ncol, nrow);
-    for (int e = edge_lane((TY + 2) * T3_W2); e < ncol + nrow; e += NT) {
-      int x, y;
-      edge_node(e, xl, xh, yl, yh, ncol, x, y);
-      const uint32_t unknown = tl_unknown(x, y, nx, ny);
-      const int lxs[3] = {min(x + 1, nx - 1) - x0 + 2, x - x0 + 2, max(x - 1, 0) - x0 + 2};
-      const int lys[3] = {min(y + 1, ny - 1) - y0 + 2, y - y0 + 2, max(y - 1, 0) - y0 + 2};
-      R g[9];
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        const R v = C::dec(lds1[i][lys[1 + kCy[i]]][lxs[1 + kCx[i]]], Ld.ds[i]);
-        g[i] = (unknown >> i) & 1u ? R(0) : v;
-      }
-      nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom1), rho0, b, Ld.corr_mode);
-      collide<R, CM>(Ld, g, rho0, b, omega);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) lds2[i][y - y0 + 1][x - x0 + 1] = C::enc(g[i], Ld.es[i]);
-    }
-  }
-  __syncthreads();
-
-  // ---- level t + 3 on the tile from lds2 (lattice node (x, y) at lds2[.][y - y0 + 1][x - x0 + 1])
-  {
-    auto pops2 = [&](int xx, int yy, R q[9]) {
-      const int lx = xx - x0 + 1, ly = yy - y0 + 1;
-#pragma unroll
-      for (int i = 0; i < 9; ++i) q[i] = C::dec(lds2[i][ly][lx], Ld.ds[i]);
-    };
-    auto mom2 = [&](int xx, int yy, R m[3]) {
-      R q[9];
-      pops2(xx, yy, q);
-      moments<R>(q, rho0, b, m[0], m[1], m[2]);
-    };
-    closure(x0, y0, TL_TX, TY, &lds2[0][0][0], (TY + 2) * T3_W2, T3_W2, x0 - 1, y0 - 1, 3);
-    level3(b, std::true_type{});
-    int xl, xh, yl, yh, ncol, nrow;
-    edge_count(x0, y0, TL_TX, TY, xl, xh, yl, yh, ncol, nrow);
-    for (int e = edge_lane(TY * TL_TX); e < ncol + nrow; e += NT) {
-      int x, y;
-      edge_node(e, xl, xh, yl, yh, ncol, x, y);
-      const uint32_t unknown = tl_unknown(x, y, nx, ny);
-      const int lxs[3] = {min(x + 1, nx - 1) - x0 + 1, x - x0 + 1, max(x - 1, 0) - x0 + 1};
-      const int lys[3] = {min(y + 1, ny - 1) - y0 + 1, y - y0 + 1, max(y - 1, 0) - y0 + 1};
-      R g[9];
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        const R v = C::dec(lds2[i][lys[1 + kCy[i]]][lxs[1 + kCx[i]]], Ld.ds[i]);
-        g[i] = (unknown >> i) & 1u ? R(0) : v;
-      }
-      nsbc_assign_correct<R>(g, unknown, edge_mc(e, x, y, mom2), rho0, b, Ld.corr_mode);
-      collide<R, CM>(Ld, g, rho0, b, omega);
-      if (x >= xo && y >= yo) store(x, y, g);
-    }
-  }
+// Tile (txi, tyi) of the 64 x TY tiling: every tile is whole, the last of a row
+// or column moved back to end at the lattice edge; it stores only the nodes its
+// neighbour does not (the overlap holds the same values in both).
+template <int S, int TY, int NT, bool NTS, int CM, bool CL = false>
+__device__ inline void three_step_tile(const LatDesc& Ld, int parity, int txi, int tyi, int part = 0) {
+  const int xo = txi * TL_TX, yo = tyi * TY;
+  three_step_tile_at<S, TL_TX, TY, TY, NT, NTS, CM, CL>(Ld, parity, min(xo, Ld.nx - TL_TX), min(yo, Ld.ny - TY), xo, yo,
+                                                        part);
 }
 
 }  // namespace lbm
