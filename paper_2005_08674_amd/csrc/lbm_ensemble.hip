@@ -373,12 +373,20 @@ int build_tiles(lbm_ens* e, int shape) {
   return LBM_OK;
 }
 
-// Two-step tile list in block order: the member-major, row-major list of
-// 64 x TY tiles is cut into 8 contiguous stretches and block b takes item
-// (b mod 8) * per + b / 8, so XCD k (block b runs on XCD b mod 8) works through
-// stretch k and neighbouring tiles share its L2; the tail pads with lat = -1.
+// Multi-step list in block order: the members' entries one member after the
+// other, XCD k (block b runs on XCD b mod 8) taking kListRun consecutive ones of
+// each 8 kListRun, so that neighbouring entries mostly share its L2 (8, 16 or 32 are
+// within 1 %, 1 is 3 % slower).  An ensemble that the eight L2s hold is cut into
+// eight stretches instead, so that each XCD finds what it wrote (BF16, 7 members, 3.9 MB
+// a buffer: 411 us per pass in runs, 392 in stretches).
 // Multi-step shapes: ids below num_two_step() are two-step shapes, the next
 // num_three_step() three-step shapes (as in the single-lattice API).
+constexpr size_t kListRun = 8, kL2Bytes = (size_t)32 << 20;
+// Tiles from which an ensemble's three-step sweep marches its larger members: two per block that the GPU holds
+// at once.  A march item runs about four times as long as a tile, which below that leaves CUs idle (us per
+// pass in tiles and marched, at tiles of 12 rows: FP64 36 members, 692 tiles 1030 and 1160; FP64 44 members, 1073 tiles
+// 685 and 622; FP16 13 members, 1143 tiles 667 and 548; FP32 14 members, 1203 tiles 420 and 367).
+constexpr size_t kMarchTiles = 1024;
 int ens_multi_count() { return lbm::num_two_step() + lbm::num_three_step(); }
 int ens_multi_steps(int id) { return id < lbm::num_two_step() ? 2 : 3; }
 
@@ -387,16 +395,24 @@ int build_two(lbm_ens* e, int id) {
   const int ty = id < n2 ? lbm::two_step_tile_rows(id) : lbm::three_step_tile_rows(id - n2);
   if (ty <= 0) return fail(LBM_ERR_ARG, "multi-step shape %d out of range", id);
   std::vector<lbm::TwoTile> items;
+  size_t ntiles = 0;
+  for (const auto& p : e->p) ntiles += (size_t)((p.nx + lbm::TL_TX - 1) / lbm::TL_TX) * ((p.ny + ty - 1) / ty);
   for (int32_t k = 0; k < e->count; ++k) {
+    if (id >= n2) {
+      lbm::ens_three_step_items(id - n2, k, e->p[k].nx, e->p[k].ny, ntiles >= kMarchTiles, items);
+      continue;
+    }
     const int tx = (e->p[k].nx + lbm::TL_TX - 1) / lbm::TL_TX, tyn = (e->p[k].ny + ty - 1) / ty;
     for (int j = 0; j < tyn; ++j)
       for (int i = 0; i < tx; ++i) items.push_back({k, i, j, 0});
   }
-  const size_t n = items.size(), per = (n + 7) / 8;
-  std::vector<lbm::TwoTile> list(8 * per, lbm::TwoTile{-1, 0, 0, 0});
-  for (size_t b = 0; b < list.size(); ++b) {
-    const size_t item = (b & 7) * per + (b >> 3);
-    if (item < n) list[b] = items[item];
+  size_t bytes = 0;
+  for (const auto& l : e->lay.lat) bytes += 2 * l.buf_bytes;
+  const size_t n = items.size(), run = bytes > kL2Bytes ? 8 * kListRun : n;
+  std::vector<lbm::TwoTile> list(n);
+  for (size_t b = 0; b < n; ++b) {
+    const size_t first = b / run * run, len = std::min(run, n - first), k = b - first, x = k & 7;
+    list[b] = items[first + x * (len / 8) + std::min(x, len & 7) + (k >> 3)];
   }
   if (list.size() > e->lay.max_two) return fail(LBM_ERR_STATE, "two-step list overflow");
   HIPCHK(hipMemcpyAsync(e->d_two, list.data(), sizeof(lbm::TwoTile) * list.size(), hipMemcpyHostToDevice,

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <vector>
 
 #include "lbm_device.h"
 
@@ -51,10 +52,13 @@ int deep_steps(int id);
 int64_t deep_tiles(const LatDesc& L, int id);
 bool deep_supported(const LatDesc& L, int id);
 hipError_t launch_deep(const LatDesc& L, int parity, int id, int k, hipStream_t s);
-// ensemble two-step: one block per list entry (member, 64-column tile x, tile y); lat < 0 = padding
+// ensemble multi-step: one block per list entry (member, 64-column tile x, tile y; three-step entries with
+// pad != 0 see k_ens_three_step)
 struct TwoTile {
   int32_t lat, txi, tyi, pad;
 };
+// entries of member `lat` in three-step shape id's list (their meaning: k_ens_three_step)
+void ens_three_step_items(int id, int lat, int nx, int ny, bool march, std::vector<TwoTile>& items);
 hipError_t launch_ens_two_step(int store, int id, const LatDesc* d, const TwoTile* list, int n, int parity,
                                hipStream_t s);
 // the same over the three-step shapes (id among the three-step shapes)

@@ -134,18 +134,35 @@ constexpr int ring_row_tx() {
   return CL ? 32 : TL_TX;
 }
 // Edge tile b of a march; the block of a number past the last leaves.
+// (Its position, and whether it is a side tile; false past the last.)
+template <int TY, int RX>
+__host__ __device__ inline bool march_ring_pos(int b, int nx, int ny, const MarchGeom& m, int& x0, int& y0, int& xo,
+                                               int& yo, bool& side) {
+  side = b >= 2 * m.across;
+  if (!side) {
+    const int top = b >= m.across;
+    xo = RX * (top ? b - m.across : b);
+    yo = y0 = top ? ny - TY : 0;
+    x0 = xo < nx - RX ? xo : nx - RX;
+  } else {
+    const int e = b - 2 * m.across;
+    x0 = xo = (e & 1) ? nx - EDGE_TX : 0;
+    yo = TY + 4 * TY * (e >> 1);
+    y0 = yo < ny - 5 * TY ? yo : ny - 5 * TY;
+  }
+  return b < m.ring();
+}
 template <int S, int TY, int NT, bool NTS, int CM, bool CL>
 __device__ __attribute__((always_inline)) inline void march_ring_tile(const LatDesc& L, int parity, int b,
                                                                       const MarchGeom& m) {
   constexpr int RX = ring_row_tx<CL>();
-  const int nx = L.nx, ny = L.ny;
-  if (b < 2 * m.across) {
-    const int top = b >= m.across, xo = RX * (top ? b - m.across : b), y0 = top ? ny - TY : 0;
-    three_step_tile_at<S, RX, TY, TY, NT, NTS, CM, CL>(L, parity, min(xo, nx - RX), y0, xo, y0, 2);
-  } else if (b < m.ring()) {
-    const int e = b - 2 * m.across, x0 = (e & 1) ? nx - EDGE_TX : 0, yo = TY + 4 * TY * (e >> 1);
-    three_step_tile_at<S, EDGE_TX, 4 * TY, TY, NT, NTS, CM, CL>(L, parity, x0, min(yo, ny - 5 * TY), x0, yo, 2);
-  }
+  int x0, y0, xo, yo;
+  bool side;
+  if (!march_ring_pos<TY, RX>(b, L.nx, L.ny, m, x0, y0, xo, yo, side)) return;
+  if (side)
+    three_step_tile_at<S, EDGE_TX, 4 * TY, TY, NT, NTS, CM, CL>(L, parity, x0, y0, xo, yo, 2);
+  else
+    three_step_tile_at<S, RX, TY, TY, NT, NTS, CM, CL>(L, parity, x0, y0, xo, yo, 2);
 }
 
 // The march items of a launch part (strip sx of ix, chunk c of chunks):
@@ -318,7 +335,7 @@ __host__ __device__ inline int march_row(int c, int rows, int chunks) {
 }
 
 // Column march (TY: the level arrays' tile rows): the block owns the 64
-// columns xs .. xs + 63 of output rows ya .. yb - 1, all inside the inner
+// columns xs .. xs + 63 (strip sx) of output rows ya .. yb - 1, all inside the inner
 // tiles' rectangle (no clamp, no NSBC), and walks down them in rounds of MR
 // rows: round j computes level t + 1 on rows ya - 2 + j MR + [0, MR) (68
 // columns, pulled from HBM), level t + 2 one row behind (66 columns) and
@@ -330,8 +347,8 @@ __host__ __device__ inline int march_row(int c, int rows, int chunks) {
 // ahead of their use: those of round j + PF are issued before round j's
 // levels t + 2 and t + 3.  Per node the arithmetic and the codec rounding
 // are the tiles': bit-identical to single steps.
-template <int S, int TY, int MR, int NT, bool NTS, int CM, int PF>
-__device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, int ya, int yb) {
+template <int S, int TY, int MR, int NT, bool NTS, int CM, int PF, bool CUT = false>
+__device__ inline void three_step_march(const LatDesc& Ld, int parity, int sx, int ya, int yb) {
   static_assert(MR >= 5 && MR <= TY && (PF == 1 || PF == 2), "march shape");
   using C = Codec<S>;
   using T = typename C::T;
@@ -339,6 +356,11 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
   constexpr int RR = MR + 2;
   constexpr int NI = (MR * T3_W1 + NT - 1) / NT;
   const int tid = threadIdx.x;
+  // the strip's first column; with CUT it loads and stores only what its neighbours do not (columns
+  // c0 .. c1 - 1 of 64): for the lattices of a few strips of an ensemble (256 of 64^2 to 512^2 FP32
+  // 460 -> 440 us per launch), while on 4096^2, where 1 column in 64 is shared, FP16 took 3 % longer
+  const int xs = min(max(TL_TX * sx, EDGE_TX), Ld.nx - EDGE_TX - TL_TX);
+  const int c0 = max(TL_TX * sx, EDGE_TX) - xs, c1 = min(TL_TX * (sx + 1) - xs, TL_TX);
   const T* __restrict__ A = static_cast<const T*>(buf_of(Ld, parity));
   T* __restrict__ B = static_cast<T*>(buf_of(Ld, parity ^ 1));
   const int pitch = Ld.pitch;
@@ -352,8 +374,8 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int k = tid + it * NT;
-      if (k < n * T3_W1) {
-        const int r = k / T3_W1, cx = k - r * T3_W1;
+      const int r = k / T3_W1, cx = k - r * T3_W1;
+      if (k < n * T3_W1 && (!CUT || (cx >= c0 && cx < c1 + 4))) {
         const uint32_t idx = (uint32_t)((q + r) * pitch + (xs - 2 + cx));
         const uint32_t ro[3] = {(idx + (uint32_t)pitch) * (uint32_t)sizeof(T), idx * (uint32_t)sizeof(T),
                                 (idx - (uint32_t)pitch) * (uint32_t)sizeof(T)};
@@ -420,8 +442,8 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int xs, i
 #pragma unroll
     for (int it = 0; it < (N3 + NT - 1) / NT; ++it) {
       const int k = tid + it * NT;
-      if (k < (hi - lo) * TL_TX) {
-        const int r = k / TL_TX, cx = k - r * TL_TX;
+      const int r = k / TL_TX, cx = k - r * TL_TX;
+      if (k < (hi - lo) * TL_TX && (!CUT || (cx >= c0 && cx < c1))) {
         const int s0 = wrap(su + r);
         const int sm = s0 == 0 ? RR - 1 : s0 - 1, sp = s0 == RR - 1 ? 0 : s0 + 1;
         const uint32_t om = (uint32_t)(sm * T3_W2 + cx + 1), o0 = (uint32_t)(s0 * T3_W2 + cx + 1),
@@ -490,8 +512,8 @@ __global__ __launch_bounds__(NT, two_step_waves<S>()) void k_three_march(LatDesc
   // (ring8 is a multiple of 8, so m and b run on the same XCD)
   int c, sx;
   if (!march_item(b - ring8, g.ix, chunks, part, c, sx, 2)) return;
-  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, min(max(TL_TX * sx, EDGE_TX), L.nx - EDGE_TX - TL_TX),
-                                               TY + march_row(c, g.rows, chunks), TY + march_row(c + 1, g.rows, chunks));
+  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, sx, TY + march_row(c, g.rows, chunks),
+                                               TY + march_row(c + 1, g.rows, chunks));
 }
 
 // One launch: the edge tiles (unless !ring: a closure lattice's run in the

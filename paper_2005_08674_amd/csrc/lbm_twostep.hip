@@ -5,6 +5,8 @@
 // and their host-side launchers.
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include <cstdio>
 
 #include "lbm_device.h"
@@ -260,15 +262,21 @@ hipError_t launch_three_step(const LatDesc& L, int parity, int id, hipStream_t s
 }
 
 // ------------------------------------------------------------------ ensemble
+// Whether an ensemble's three-step sweep in tiles of `ty` rows marches its larger members (the rows
+// that the single-lattice marches use), and in chunks of about how many rows.  256 members of 64^2 to 512^2
+// in FP32, us per launch: tiles 505 to 520; marched in chunks of 18 / 29 / 40 / 62 / 96 rows 464 / 441 / 439 /
+// 454 / 468 (12 rows, 768 threads) and 445 / 441 / 447 / 461 / 480 (8 rows).  Longer chunks recompute
+// fewer rows, but leave the edge tiles of their own member to other times.
+constexpr bool ens_marches(int ty) { return ty == 8 || ty == 12; }
+constexpr int ens_march_rows(int ty) { return ty == 12 ? 40 : 29; }
+
 // One block per entry of a device list of (member, tile) in block order (the
-// host lays the list out so that each XCD takes a contiguous stretch of it);
-// entries with lat < 0 pad the grid.  The member's descriptor carries its
-// collision model, read at run time.
+// host lays the list out so that each XCD takes short runs of neighbours).  The
+// member's descriptor carries its collision model, read at run time.
 template <int S, int TY, int NT, bool NTS>
 __global__ __launch_bounds__(NT, two_step_waves<S>()) void k_ens_two_step(const LatDesc* __restrict__ descs,
                                                      const TwoTile* __restrict__ list, int parity) {
   const TwoTile t = list[blockIdx.x];
-  if (t.lat < 0) return;  // padding: the whole block leaves before any barrier
   const LatDesc L = descs[t.lat];
   two_step_tile<S, TY, NT, NTS, -1>(L, parity, t.txi, t.tyi);
 }
@@ -281,14 +289,50 @@ int two_step_min_rows() {
   return m;
 }
 
-// Three-step sweep over an ensemble's tile list (as k_ens_two_step).
+// Three-step sweep over an ensemble's list (as k_ens_two_step).  An entry is a 64 x TY
+// tile of a member (pad == 0); where the member is large enough to march
+// (MarchGeom), its edge tiles (pad == -1, txi the number) and its strips' chunks (txi the
+// strip, output rows tyi .. pad - 1) take the place of its tiles.
 template <int S, int TY, int NT, bool NTS>
 __global__ __launch_bounds__(NT, two_step_waves<S>()) void k_ens_three_step(const LatDesc* __restrict__ descs,
                                                        const TwoTile* __restrict__ list, int parity) {
   const TwoTile t = list[blockIdx.x];
-  if (t.lat < 0) return;  // padding: the whole block leaves before any barrier
   const LatDesc L = descs[t.lat];
-  three_step_tile<S, TY, NT, NTS, -1>(L, parity, t.txi, t.tyi);
+  if constexpr (ens_marches(TY)) {
+    if (t.pad > 0) {
+      three_step_march<S, TY, TY - 1, NT, NTS, -1, 1, true>(L, parity, t.txi, t.tyi, t.pad);
+      return;
+    }
+    int xo = t.txi * TL_TX, yo = t.tyi * TY, x0 = min(xo, L.nx - TL_TX), y0 = min(yo, L.ny - TY);
+    if (t.pad < 0) {
+      bool side;
+      march_ring_pos<TY, TL_TX>(t.txi, L.nx, L.ny, MarchGeom(L.nx, L.ny, TY), x0, y0, xo, yo, side);
+      if (side) {
+        three_step_tile_at<S, EDGE_TX, 4 * TY, TY, NT, NTS, -1>(L, parity, x0, y0, xo, yo, 2);
+        return;
+      }
+    }
+    three_step_tile_at<S, TL_TX, TY, TY, NT, NTS, -1>(L, parity, x0, y0, xo, yo, 0);
+  } else {
+    three_step_tile<S, TY, NT, NTS, -1>(L, parity, t.txi, t.tyi);
+  }
+}
+
+// The entries of member `lat` (nx x ny) in three-step shape `id`'s list, marched where `march` and its
+// size allow.
+void ens_three_step_items(int id, int lat, int nx, int ny, bool march, std::vector<TwoTile>& items) {
+  const int ty = kThree[id].ty;
+  const MarchGeom g(nx, ny, ty);
+  if (march && ens_marches(ty) && g.ix > 0) {
+    const int chunks = march_chunks(g.rows, ens_march_rows(ty));
+    for (int b = 0; b < g.ring(); ++b) items.push_back({lat, b, 0, -1});
+    for (int c = 0; c < chunks; ++c)
+      for (int sx = 0; sx < g.ix; ++sx)
+        items.push_back({lat, sx, ty + march_row(c, g.rows, chunks), ty + march_row(c + 1, g.rows, chunks)});
+    return;
+  }
+  for (int j = 0; j < (ny + ty - 1) / ty; ++j)
+    for (int i = 0; i < (nx + TL_TX - 1) / TL_TX; ++i) items.push_back({lat, i, j, 0});
 }
 
 int three_step_tile_rows(int id) { return id >= 0 && id < kNumThree ? kThree[id].ty : 0; }

@@ -73,3 +73,29 @@ def test_march_edges_with_closure_equal_single_steps(store):
             assert torch.equal(g.populations(), want), (nx, ny, name)
             g.close()
         ref.close()
+
+
+@pytest.mark.parametrize("store", ["f64", "f32", "f16", "bf16"])
+def test_ensemble_of_marched_and_tiled_members_equals_single_steps(store):
+    """Members on both sides of the size from which an ensemble's three-step sweep marches, BGK and MRT."""
+    from paper_2005_08674_amd.ensemble import Ensemble, member_params
+    members, fields = [], []
+    for k, (nx, ny) in enumerate(SIZES + [(64, 20), (300, 64)]):
+        members.append(member_params(nx, ny, 0.57, store=store, mrt=(1.6, 1.4, 1.8) if k % 3 == 2 else None))
+        r = np.random.default_rng(nx * 7 + ny)
+        fields.append(tuple(1e-3 * r.standard_normal((ny, nx)) for _ in range(3)))
+    ref = Ensemble(members, fields)
+    ref.step(12)
+    want = [ref.populations(m) for m in range(len(members))]
+    ref.close()
+    for shape in range(L.lbm_two_step_count()):
+        name = L.lbm_two_step_describe(shape)
+        if not (name.startswith("3step:64x12") or name.startswith("3step:64x8")) or "+march" in name:
+            continue
+        e = Ensemble(members, fields)
+        e.set_two_step(shape)
+        e.step(6)
+        e.step_graph(6)
+        for m in range(len(members)):
+            assert np.array_equal(e.populations(m), want[m]), (members[m].nx, members[m].ny, name)
+        e.close()
