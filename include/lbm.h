@@ -144,7 +144,9 @@ int lbm_set_velocity_edge(lbm_ctx* ctx, double ux, double uy);
  * lbm_autotune_two_step) and while fusion is on, overlap, per-kernel timing
  * and the closure off, the library picks the launches of n >= 2 steps by the
  * lattice's size, edges and storage: several steps per launch, with the
- * results of single steps, bit for bit.  The call is a
+ * results of single steps, bit for bit.  A call recorded into a HIP graph
+ * keeps to one launch per step, so that a graph of an even number of steps
+ * can be replayed to go on stepping.  The call is a
  * roctx range named "lbm_step" (as are the other stepping and tuning calls,
  * each under its own name), visible to rocprofv3 --marker-trace. */
 int lbm_step(lbm_ctx* ctx, int32_t n);

@@ -525,9 +525,21 @@ int rem_shape(const lbm_ctx* c, int k) {
   return -1;
 }
 
+// Whether work on the context's stream is being recorded into a graph (or
+// that cannot be told).
+bool capturing(const lbm_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Whether lbm_step chooses its launches by itself: nobody has chosen one, and
-// nothing asks for the single-step kernels (timing counts their launches).
-bool free_choice(const lbm_ctx* c) { return !c->chosen && !c->timing && use_fused(c); }
+// nothing asks for the single-step kernels.  Timing counts their launches.  A
+// graph of an even number of single steps ends in the buffer that it started
+// from, so that a replay continues the last one; several steps per launch would
+// end in the other buffer and every replay would repeat the same steps.
+bool free_choice(const lbm_ctx* c) { return !c->chosen && !c->timing && use_fused(c) && !capturing(c); }
 
 // Multi-step shape of a free lattice with four NSBC edges, -1 for the deep
 // sweep.  The 64-wide sweeps recompute less margin per step than the deep one
