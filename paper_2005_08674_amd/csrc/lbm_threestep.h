@@ -175,7 +175,9 @@ __device__ __attribute__((always_inline)) inline void march_ring_tile(const LatD
 // mostly share an L2, and the eight XCDs stream through the same rows.  With an
 // eighth of the list each they had eight regions open in memory (4096^2 us per step,
 // FP32 84.6 -> 83.1, with loads two rounds ahead 85.2 -> 80.4; FP64 172.7 -> 167.3; 4 or 16
-// items are within 1 %, 1 is 10 % slower).
+// items are within 1 %, 1 is 10 % slower).  A shorter last run is split evenly: eight
+// more items on one XCD than on another are a round of blocks more where a lattice
+// takes one or two (1000 x 999 FP64 in 11 chunks 15.2 -> 12.8, MRT 19.0 -> 14.9).
 constexpr int MARCH_RUN = 8;
 __host__ __device__ inline int march_part_items(int ix, int chunks, int part, int rb = 1) {
   const int fx = ix - 1 - rb, fc = chunks - 2;
@@ -186,9 +188,10 @@ __host__ __device__ inline int march_blocks(int items) {
   return (items + 8 * MARCH_RUN - 1) / (8 * MARCH_RUN) * (8 * MARCH_RUN);
 }
 __host__ __device__ inline bool march_item(int m, int ix, int chunks, int part, int& c, int& sx, int rb = 1) {
-  const int items = march_part_items(ix, chunks, part, rb);
-  const int item = (m & ~(8 * MARCH_RUN - 1)) + (m & 7) * MARCH_RUN + ((m >> 3) & (MARCH_RUN - 1));
-  if (item >= items) return false;
+  const int run = m & ~(8 * MARCH_RUN - 1), x = m & 7, j = (m - run) >> 3;
+  const int left = march_part_items(ix, chunks, part, rb) - run, len = left < 8 * MARCH_RUN ? left : 8 * MARCH_RUN;
+  if (j >= (len >> 3) + (x < (len & 7))) return false;
+  const int item = run + x * (len >> 3) + (x < (len & 7) ? x : len & 7) + j;
   const int fx = ix - 1 - rb, fc = chunks - 2;
   if (part == 1) {
     c = 1 + item / fx;
@@ -200,10 +203,9 @@ __host__ __device__ inline bool march_item(int m, int ix, int chunks, int part, 
     c = 0;
     sx = item;
   } else if (item < ix + (1 + rb) * fc) {
-    const int k = item - ix;
-    c = 1 + k / (1 + rb);
-    const int j = k % (1 + rb);
-    sx = j == 0 ? 0 : ix - 1 - rb + j;
+    const int e = item - ix, b = e % (1 + rb);
+    c = 1 + e / (1 + rb);
+    sx = b == 0 ? 0 : ix - 1 - rb + b;
   } else {
     c = chunks - 1;
     sx = item - ix - (1 + rb) * fc;
@@ -332,6 +334,24 @@ inline bool three_step_fits_store(int store, int id, bool closure) {
 __host__ __device__ inline int march_chunks(int rows, int h) { return (rows + h - 1) / h; }
 __host__ __device__ inline int march_row(int c, int rows, int chunks) {
   return (int)((int64_t)c * rows / chunks);
+}
+
+// Chunks of a march of `ix` strips beside `ring` blocks of edge tiles on a GPU that holds `slots` blocks (256 CUs):
+// those of about h rows, but more where they leave CUs without one -- as many as fill the blocks' one
+// or two rounds, of at least 2 MR - 4 rows, the output of two rounds of the march.  Where that is little more (and
+// the CUs have equal numbers of them), shorter chunks cost more margin than they win.  us per step
+// before and after, chunks of 64 rows: FP32 700 x 701 5.6 / 4.3, 1000 x 999 8.2 / 6.7, 1448^2 14.1 / 12.7;
+// FP16 1000 x 999 6.7 / 5.6; of 128 rows FP32 1448^2 16.4 / 13.5; 2048 x 1024 would take 12.9 / 13.3.
+// A few blocks more than a round holds are avoided by slightly longer chunks.
+template <int MR>
+inline int march_chunks_filled(int ix, int rows, int h, int ring, int slots) {
+  const int chunks = march_chunks(rows, h), items = ix * chunks, rounds = (items + slots - 1) / slots;
+  if (rounds > 2) return chunks;
+  const int by_slots = (rounds * slots - ring) / ix, by_rows = rows / (2 * MR - 4);
+  const int most = by_slots < by_rows ? by_slots : by_rows;
+  const int cus = (items + 255) / 256 * 256;
+  if (2 * most > 3 * chunks || (5 * cus >= 6 * items && most > chunks)) return most;
+  return by_slots < chunks && 8 * by_slots >= 7 * chunks ? by_slots : chunks;
 }
 
 // Column march (TY: the level arrays' tile rows): the block owns the 64
@@ -527,7 +547,12 @@ inline hipError_t launch_march_t(const LatDesc& L, int parity, hipStream_t s, in
   } else {
     const MarchGeom g(L.nx, L.ny, TY);
     if (g.ix == 0) return hipErrorInvalidValue;
-    const int ring8 = ring ? (g.ring() + 7) / 8 * 8 : 0, chunks = march_chunks(g.rows, h);
+    // blocks that a CU holds: its LDS, and the waves of the register budget (two_step_waves; FP64 four a SIMD)
+    constexpr int by_lds = 160 * 1024 / three_step_lds_bytes<S, TY>(), by_waves = (S == ST_F64 ? 16 : 24) / (NT / 64);
+    constexpr int slots = 256 * (by_lds < by_waves ? by_lds : by_waves);
+    // (a closure lattice's two parts keep one length of chunk)
+    const int ring8 = ring ? (g.ring() + 7) / 8 * 8 : 0;
+    const int chunks = ring ? march_chunks_filled<MR>(g.ix, g.rows, h, ring8, slots) : march_chunks(g.rows, h);
     const int items = march_part_items(g.ix, chunks, part, 2);
     if (ring8 + items == 0) return hipSuccess;
     const dim3 grid(ring8 + march_blocks(items));
