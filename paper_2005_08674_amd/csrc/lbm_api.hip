@@ -516,10 +516,9 @@ int rem_shape(const lbm_ctx* c, int k) {
   if (k < 2 || k > 4) return -1;
   if (c->rem_best[k] >= 0 && multi_supported(c->L, c->rem_best[k])) return c->rem_best[k];
   if (k == 2) {
-    const char* want = c->p.store == LBM_STORE_F64   ? "2step:64x12/512+xcdband+nts"
-                       : c->p.store == LBM_STORE_F32 ? "2step:64x20/768+xcdband+nts"
-                                                     : "2step:64x8/512+march7xh96+xcdband+nts";
-    const int id = multi_named(want);
+    static const int f64 = multi_named("2step:64x12/512+xcdband+nts"), f32 = multi_named("2step:64x20/768+xcdband+nts"),
+                     half = multi_named("2step:64x8/512+march7xh96+xcdband+nts");
+    const int id = c->p.store == LBM_STORE_F64 ? f64 : (c->p.store == LBM_STORE_F32 ? f32 : half);
     if (multi_supported(c->L, id)) return id;
   }
   return -1;
@@ -541,22 +540,41 @@ bool capturing(const lbm_ctx* c) {
 // end in the other buffer and every replay would repeat the same steps.
 bool free_choice(const lbm_ctx* c) { return !c->chosen && !c->timing && use_fused(c) && !capturing(c); }
 
-// Multi-step shape of a free lattice with four NSBC edges, -1 for the deep
-// sweep.  The 64-wide sweeps recompute less margin per step than the deep one
-// but take few blocks: measured, us per step in runs of 60 (three-step tiles /
-// march / best deep shape), they win from 2048^2 on in FP64 (50 / 46 / 60) and
-// FP32 (25 / 24 / 33) and trail or tie below (1024 x 1024: 14.9 / 15.8 / 14.4
-// and 8.3 / 9.2 / 8.7; in runs of 10, where three steps leave a remainder, the
-// deep sweep is ahead throughout); the 16-bit formats, whose deep sweep pays
-// for its conversions, change at 2^19 nodes (512^2: 3.7 / 6.2 / 3.9, 701^2: 4.4 /
-// 6.5 / 5.7).
-int free_multi(const lbm_ctx* c) {
-  const int64_t nodes = (int64_t)c->p.nx * c->p.ny;
-  const bool half = c->lay.esize == 2;
-  if (nodes < (half ? (int64_t)1 << 19 : (int64_t)1 << 21)) return -1;
-  const int id = multi_named(nodes < (int64_t)1 << 21 ? "3step:64x12/768+xcdband+nts"
-                                                      : "3step:64x12/768+march11xh96+xcdband+nts");
+// What the rules of a free lattice look at besides the number of steps.
+int64_t nodes_of(const lbm_ctx* c) { return (int64_t)c->p.nx * c->p.ny; }
+bool is_half(const lbm_ctx* c) { return c->lay.esize == 2; }
+// more arithmetic per update than BGK about rest
+bool is_heavy(const lbm_ctx* c) { return c->L.coll == lbm::COLL_MRT || !c->L.ub_zero; }
+
+// Multi-step shape of a free lattice with four NSBC edges for n steps, -1 for
+// the deep sweep or single steps.  The 64-wide sweeps recompute less margin per
+// step than the deep one but take few blocks; a single step that they leave costs
+// as much as two or three of theirs, and two steps are one deep launch.  us per
+// step in long runs, three-step tiles / march / deep sweep / single steps: FP32 512^2
+// 3.1 / 3.2 / 3.8 / 9.2, 701^2 4.6 / 4.5 / 5.2 / 12.1, 820^2 6.0 / 5.2 / 6.2 / 13.7, 1000 x
+// 999 7.8 / 6.7 / 8.6 / 16.7; FP16 512^2 3.4 / 4.2 / 4.2 / 8.2, 1000 x 999 7.0 / 5.7 / 9.0 /
+// 12.4; FP64 512^2 6.5 / - / 5.3 / 12.0, 1000 x 999 16.7 / 12.9 / 14.6 / 30.8, 2048^2 59 /
+// 41 / 60 / 106.  In runs of 4 (3 + 1 steps against one deep launch) FP16 512^2 5.1 / 4.5,
+// 701^2 6.5 / 5.7; of 10 FP32 512^2 4.0 / 3.7; of 2 (a two-step launch) FP64 1000 x 1024
+// 25 / 20, FP32 13.4 / 13.0.
+int free_multi(const lbm_ctx* c, int n) {
+  const int64_t nodes = nodes_of(c);
+  const bool f32 = c->p.store == LBM_STORE_F32;
+  if (nodes < (c->p.store == LBM_STORE_F64 ? (int64_t)1 << 19 : (int64_t)1 << 18)) return -1;
+  if ((n == 2 || n == 4) && nodes < (is_half(c) ? (int64_t)1 << 19 : (int64_t)1 << 21)) return -1;
+  if ((n == 7 || n == 10) && f32 && nodes < (int64_t)1 << 19) return -1;
+  static const int tiles = multi_named("3step:64x8/512+xcdband+nts"),
+                   march = multi_named("3step:64x12/768+march11xh96+xcdband+nts");
+  const int id = nodes < (int64_t)1 << 19 ? tiles : march;
   return multi_supported(c->L, id) ? id : -1;
+}
+
+// Whether a free lattice takes a two-step launch for two steps that its
+// three-step launches leave (us per step against single steps: FP16 MRT 1000 x 1024
+// 14.9 / 12.6, 2048 x 1024 21.1 / 20.0, 2048^2 31 / 39; FP16 BGK at rest 100 x 6000
+// 14.5 / 13.5, 820^2 10.6 / 10.4, 2048 x 1024 16.2 / 18.5).
+bool free_two_pays(const lbm_ctx* c) {
+  return !is_half(c) || nodes_of(c) >= (is_heavy(c) ? (int64_t)1 << 22 : (int64_t)1 << 20);
 }
 
 // Deep-sweep shape of a free lattice: the smallest tile whose blocks are all
@@ -576,22 +594,53 @@ int deep_shape(const lbm_ctx* c) {
   return id;
 }
 
-// n steps in as few deep launches as they take, of nearly equal length.
-int step_deep(lbm_ctx* c, int id, int n) {
-  for (int m = (n + lbm::deep_steps(id) - 1) / lbm::deep_steps(id); m > 0; --m) {
-    const int k = (n + m - 1) / m;
+// Fewest steps that one deep launch does faster than single steps do, 0 if it
+// never does.  A launch's first level costs about four of the others, and the
+// 16-bit formats pay for their conversions at every level, while single steps
+// get cheaper with the bytes.  us per step in launches of 2 / 3 / 4 steps against
+// single steps, channel edges:
+//   FP64 4096^2 330 / 272 / 232 against 446 (MRT 369 / 321 / 289 against 460), and with
+//   a base velocity on 100 x 6000, where many tiles hold edge nodes, 26.9 / 21.9 / 19.4
+//   against 24.5;
+//   FP32 4096^2 173 / 152 / 126 against 203; with a base velocity 1000 x 1024 16.0 /
+//   12.3 / 10.8 against 16.8, 2048^2 59 / 47 / 39 against 56, and in 768 to 1024 tiles
+//   of 16 x 16, short of two rounds, 3000 x 80 8.9 / 6.2 / 5.4 against 8.8;
+//   FP16 701^2 8.3 / 6.5 / 5.5 against 9.5, 1000 x 1024 13.4 / 10.4 / 9.2 against 12.4,
+//   3001 x 2047 60 / 47 / 39 against 46, 4096^2 160 / 129 / 108 against 108;
+//   FP16 MRT 512^2 6.9 / 5.9 / 5.4 against 8.4, 701^2 10.0 / 8.0 / 7.0 against 9.7,
+//   1000 x 1024 16.5 / 13.2 / 12.2 against 12.5, 2048 x 1024 28 / 23 / 21 against 20;
+//   FP16 with a base velocity 3000 x 80 8.0 / 5.8 / 5.1 against 7.8 (on four NSBC edges
+//   10.0 / 7.0 / 6.1), 1000 x 1024 16.7 / 13.2 / 11.5 against 12.6.
+int deep_min_steps(const lbm_ctx* c) {
+  const int64_t nodes = nodes_of(c), k = 1 << 16;
+  if (c->p.store == LBM_STORE_F64) return c->L.ub_zero || std::min(c->p.nx, c->p.ny) >= 128 ? 2 : 3;
+  if (c->p.store == LBM_STORE_F32)
+    return c->L.ub_zero || nodes <= 3 * k || (nodes > 4 * k && nodes < 64 * k) ? 2 : 3;
+  if (is_heavy(c)) {
+    if (nodes <= (c->L.ub_zero ? 4 : 3) * k) return 2;
+    return nodes < 8 * k ? 3 : (nodes < 24 * k ? 4 : 0);
+  }
+  return nodes < 8 * k ? 2 : (nodes < 80 * k ? 3 : (nodes < 128 * k ? 4 : 0));
+}
+
+// Up to n steps in deep launches, *done of them: as few launches as they take
+// and of nearly equal length if each pays, else full ones and what is left of
+// them if that pays.
+int step_deep(lbm_ctx* c, int id, int n, int* done) {
+  const int km = lbm::deep_steps(id), least = deep_min_steps(c);
+  *done = 0;
+  if (least == 0 || least > km) return LBM_OK;
+  const int m = (n + km - 1) / km;
+  const bool even = n / m >= least;
+  const int left = n % km, launches = even ? m : n / km + (left >= least);
+  for (int j = 0; j < launches; ++j) {
+    const int k = even ? (n - *done + launches - j - 1) / (launches - j) : std::min(km, n - *done);
     HIPCHK(lbm::launch_deep(c->L, c->parity, id, k, c->stream));
     c->parity ^= 1;
     c->t += k;
-    n -= k;
+    *done += k;
   }
   return LBM_OK;
-}
-
-// The multi-step shape lbm_step takes, -1 for none.
-int use_multi(const lbm_ctx* c) {
-  const int id = free_choice(c) ? free_multi(c) : c->two_step;
-  return id >= 0 && !c->overlap && multi_supported(c->L, id) ? id : -1;
 }
 
 }  // namespace
@@ -722,13 +771,15 @@ int lbm_step(lbm_ctx* c, int32_t n) {
     HIPCHK(hipEventRecord(c->ev_edge, c->stream));
   }
   int32_t s = 0;
-  if (const int id = use_multi(c); id >= 0) {
+  const bool free = n >= 2 && free_choice(c);
+  const int id = free ? free_multi(c, n) : c->two_step;
+  if (id >= 0 && !c->overlap && multi_supported(c->L, id)) {
     const int k = multi_steps(id);
     int rc = LBM_OK;
     for (; s + k <= n && rc == LBM_OK; s += k) rc = step_multi(c, id);
     // a remainder of two or more steps: one launch of a shape with that
     // many steps instead of single steps (same results)
-    if (rc == LBM_OK && n - s >= 2) {
+    if (rc == LBM_OK && n - s >= 2 && !(free && !free_two_pays(c))) {
       const int r = rem_shape(c, n - s);
       if (r >= 0) {
         // (another shape's edge tiles may reach past this one's border)
@@ -741,11 +792,9 @@ int lbm_step(lbm_ctx* c, int32_t n) {
     const hipError_t e = settle_join(c, c->join_pending);
     if (rc) return rc;
     HIPCHK(e);
-  } else if (n >= 2 && free_choice(c)) {
-    const int id = deep_shape(c);
-    if (id >= 0) {
-      if (int rc = step_deep(c, id, n)) return rc;
-      s = n;
+  } else if (free) {
+    if (const int d = deep_shape(c); d >= 0) {
+      if (int rc = step_deep(c, d, n, &s)) return rc;
     }
   }
   for (; s < n; ++s) {
