@@ -81,13 +81,12 @@ __device__ inline void normal_frame_diff(const R a[3], const R b[3], int nx_, in
 
 // Strip amplitude of an input row,
 //   A = sqrt( (1/9) sum_j [c_s^2 (rho_j - rho_ref)^2 / rho0^2 + |u_j - u_ref|^2] ),
-// from the unscaled strip features feat(j, q) (strip node j, feature q; UNROLL of
-// the nine nodes at a time).
-template <int UNROLL = 9, class F>
+// from the unscaled strip features feat(j, q) (strip node j, feature q).
+template <class F>
 __device__ inline float strip_amplitude(F feat, float rho0) {
   constexpr float cs2 = 1.f / 3.f;
   float s = 0.f;
-#pragma unroll UNROLL
+#pragma unroll
   for (int j = 0; j < 9; ++j) {
     const float r = feat(j, 0) / rho0, un = feat(j, 1), ut = feat(j, 2);
     s += cs2 * r * r + un * un + ut * ut;
@@ -115,11 +114,11 @@ __device__ inline float input_value(int q, F feat, float inv, float omega, const
 // wave carries the two in equal measure (ratio 1 at normal incidence), a
 // convected vortex almost only the first; kmin = 0 accepts every node.  The
 // ratio does not depend on the 1/A scaling of the row.
-template <int UNROLL = 9, class F>
+template <class F>
 __device__ inline bool vortical_row(F scaled, float rho0, float kmin) {
   constexpr float cs2 = 1.f / 3.f;
   float su = 0.f, sr = 0.f;
-#pragma unroll UNROLL
+#pragma unroll
   for (int j = 0; j < 9; ++j) {
     const float r = scaled(j, 0) / rho0, un = scaled(j, 1), ut = scaled(j, 2);
     su += un * un + ut * ut;

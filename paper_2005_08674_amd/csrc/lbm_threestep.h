@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "lbm_device.h"
 #include "lbm_twostep_lds.h"
 
@@ -518,11 +520,11 @@ __device__ inline void three_step_march(const LatDesc& Ld, int parity, int sx, i
 }
 
 // Blocks below ring8 take the edge tiles (march_ring_tile, padded to a multiple
-// of 8), the others the strips' chunks (march_item).  The edge tiles come first:
+// of 8), the others the strips' chunks (march_item), each cut into `cuts` pieces.  The edge tiles come first:
 // they are the slower blocks.
 template <int S, int TY, int MR, int NT, bool NTS, int CM, int PF>
 __global__ __launch_bounds__(NT, two_step_waves<S>()) void k_three_march(LatDesc L, int parity, int ring8, int chunks,
-                                                                       int part) {
+                                                                       int part, int cuts) {
   const MarchGeom g(L.nx, L.ny, TY);
   const int b = blockIdx.x;
   if (b < ring8) {
@@ -531,9 +533,10 @@ __global__ __launch_bounds__(NT, two_step_waves<S>()) void k_three_march(LatDesc
   }
   // (ring8 is a multiple of 8, so m and b run on the same XCD)
   int c, sx;
-  if (!march_item(b - ring8, g.ix, chunks, part, c, sx, 2)) return;
-  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, sx, TY + march_row(c, g.rows, chunks),
-                                               TY + march_row(c + 1, g.rows, chunks));
+  const int all = ((int)gridDim.x - ring8) / cuts, k = (b - ring8) / all;
+  if (!march_item(b - ring8 - k * all, g.ix, chunks, part, c, sx, 2)) return;
+  const int ya = march_row(c, g.rows, chunks), h = march_row(c + 1, g.rows, chunks) - ya;
+  three_step_march<S, TY, MR, NT, NTS, CM, PF>(L, parity, sx, TY + ya + march_row(k, h, cuts), TY + ya + march_row(k + 1, h, cuts));
 }
 
 // One launch: the edge tiles (unless !ring: a closure lattice's run in the
@@ -555,11 +558,14 @@ inline hipError_t launch_march_t(const LatDesc& L, int parity, hipStream_t s, in
     const int chunks = ring ? march_chunks_filled<MR>(g.ix, g.rows, h, ring8, slots) : march_chunks(g.rows, h);
     const int items = march_part_items(g.ix, chunks, part, 2);
     if (ring8 + items == 0) return hipSuccess;
-    const dim3 grid(ring8 + march_blocks(items));
+    // a closure lattice's border is a launch of its own of a few blocks (2048^2: 192 of 61 rows in 24 us beside the
+    // middle's 64): cut down to two rounds of the march it takes as many of the GPU's blocks as there are
+    const int cuts = part == 2 ? std::max(1, g.rows / chunks / (2 * MR - 4)) : 1;
+    const dim3 grid(ring8 + march_blocks(items) * cuts);
     if (L.coll == COLL_MRT)
-      k_three_march<S, TY, MR, NT, NTS, COLL_MRT, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part);
+      k_three_march<S, TY, MR, NT, NTS, COLL_MRT, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part, cuts);
     else
-      k_three_march<S, TY, MR, NT, NTS, COLL_BGK, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part);
+      k_three_march<S, TY, MR, NT, NTS, COLL_BGK, PF><<<grid, dim3(NT), 0, s>>>(L, parity, ring8, chunks, part, cuts);
     return hipGetLastError();
   }
 }

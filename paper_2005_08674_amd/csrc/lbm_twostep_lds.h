@@ -396,11 +396,15 @@ __device__ inline void tl_edge_count(int nx, int ny, int rx0, int ry0, int rw, i
 // block.  An edge tile runs this code once per level and tile, not in a hot
 // loop, so it is kept compact (one copy for the three levels, loops rolled):
 // its instructions come from L2 on every tile, and their count, not the
-// arithmetic, sets its time.
+// arithmetic, sets its time.  The amplitude and the gate are unrolled all the
+// same: every group of nodes runs them, also where no node passes (rolled up, a
+// 1024^2 lattice in tiles took 17.5 us per step on a fresh vortex, unrolled 15.4),
+// and the weights are loaded by a wave's first group that a node passes
+// (14.8; `have` of the tile's three levels).
 template <int S, int CLW, class PopsFn>
 __device__ inline __attribute__((always_inline)) void closure_level(const LatDesc& Ld, int rx0, int ry0, int rw, int rh,
                                                                     PopsFn pops, char* scr, float* cl_y, int nt,
-                                                                    const mlp::Params& par, const mlp::Frags& weights) {
+                                                                    const mlp::Params& par, mlp::Frags& weights, bool& have) {
   using R = typename Codec<S>::R;
   const int nx = Ld.nx, ny = Ld.ny;
   const int tid = threadIdx.x;
@@ -466,10 +470,10 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
         float A = 0.f, inv = 0.f;
         bool gated = false;
         if (eligible) {
-          A = strip_amplitude<1>(fv, rho0f);
+          A = strip_amplitude(fv, rho0f);
           inv = amplitude_inverse(A);
           auto scaled = [&](int jj, int q) { return fv(jj, q) * inv; };
-          gated = vortical_row<1>(scaled, rho0f, net.kmin);
+          gated = vortical_row(scaled, rho0f, net.kmin);
         }
         if (c == 0 && valid) cl_y[4 * (base_e + i) + 3] = gated ? A : 0.f;
         if (__ballot(gated) == 0) continue;              // wave-uniform
@@ -515,6 +519,8 @@ __device__ inline __attribute__((always_inline)) void closure_level(const LatDes
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_s_waitcnt(0);
         mlp::f32x4 yv;
+        if (!have) mlp::load_frags(net, weights);
+        have = true;
         mlp::forward16(weights, par, X, H1, X, yv);
         const int col = l & 15;
         if (col < 3) {
@@ -744,7 +750,7 @@ __device__ __attribute__((always_inline)) inline void three_step_tile_at(const L
   // beside this kernel streams through (2048^2: a level of a side tile past the gate 12.5 -> 8.4 us)
   mlp::Params par{};
   mlp::Frags weights;
-  if constexpr (CL) mlp::load_frags(*static_cast<const mlp::Net*>(Ld.net), weights);
+  bool have = false;
   if constexpr (CL) par = mlp::stage_params(*static_cast<const mlp::Net*>(Ld.net), cl_par, tid, NT);
   // the closure phases of level lv (CL): region and previous level, scratch in the level array
   // not in use, or LDS of its own.  One copy of the code for the three levels.
@@ -766,7 +772,7 @@ __device__ __attribute__((always_inline)) inline void three_step_tile_at(const L
           for (int i = 0; i < 9; ++i) g[i] = C::dec(p[i * pi + idx], Ld.ds[i]);
         }
       };
-      closure_level<S, CLW>(Ld, x0 - m, y0 - m, TX + 2 * m, TY + 2 * m, pops, scr, &cl_y[0][0], NT, par, weights);
+      closure_level<S, CLW>(Ld, x0 - m, y0 - m, TX + 2 * m, TY + 2 * m, pops, scr, &cl_y[0][0], NT, par, weights, have);
     }
   };
 

@@ -39,3 +39,29 @@ def test_march_chunks_equal_single_steps(nx, ny, store):
             g.step(6)
             assert torch.equal(g.populations(), want), (name, mrt)
             g.close()
+
+
+@pytest.mark.parametrize("nx,ny,store", [(700, 701, "f32"), (417, 300, "bf16"), (330, 500, "f64")])
+def test_march_with_closure_equals_single_steps(nx, ny, store):
+    """The border of the inner part, cut into shorter pieces than the middle's chunks, with every node past the
+    gate and with few of them."""
+    from paper_2005_08674_amd.closure import Trainer
+    tr = Trainer(max_batch=64, seed=5)
+    tr.set_normalization(np.zeros(96, np.float32), np.full(96, 0.5, np.float32), np.full(3, 0.02, np.float32))
+    for kmin in (0.0, 4.0):
+        blob = tr.export(50.0, 1.0, kmin)
+        want = None
+        for shape in [-1] + [i for i in range(L.lbm_two_step_count()) if "3step" in L.lbm_two_step_describe(i)]:
+            g = _lattice(nx, ny, store, False)
+            L.lbm_set_closure(g.ctx, blob.data_ptr(), 1)
+            try:
+                L.lbm_set_two_step(g.ctx, shape)
+            except L.LbmError:
+                assert store == "f64"  # the level arrays of the taller tiles
+                g.close()
+                continue
+            g.step(9)
+            got = g.populations()
+            want = got if want is None else want
+            assert torch.equal(got, want), (kmin, shape)
+            g.close()
