@@ -151,6 +151,15 @@ int lbm_set_velocity_edge(lbm_ctx* ctx, double ux, double uy);
  * each under its own name), visible to rocprofv3 --marker-trace. */
 int lbm_step(lbm_ctx* ctx, int32_t n);
 
+/* lbm_set_auto_launch returns the context to that choice, whatever launch was
+ * selected before.  lbm_time_auto_launch times it as the tuners time their
+ * candidates: the median over `reps` runs of 24 steps, in ms per step, to *ms
+ * (the state and t are left unchanged; synchronizes the stream); -1 where the
+ * choice is single-step launches or one of the multi-step shapes, which
+ * lbm_autotune and lbm_autotune_two_step time. */
+int lbm_set_auto_launch(lbm_ctx* ctx);
+int lbm_time_auto_launch(lbm_ctx* ctx, int32_t reps, float* ms);
+
 /* Moments of every node at the current time (eqs. cf_0, cf_1): writes
  * rho - rho0 (deviation = 1) or rho (deviation = 0) to drho_out and the
  * velocity to ux_out, uy_out, each a device [ny][nx] array of float64
@@ -261,6 +270,8 @@ int lbm_energy_noalloc(lbm_ctx* test, const lbm_ctx* ref, int32_t x_off, int32_t
  * with the closure or fusion off, the bulk kernel followed by the edge
  * kernel: whole steps either way), `reps` timed runs of 24 consecutive
  * steps each, median of those, after one warm-up, and selects the fastest.
+ * A context for which no launch has been chosen and whose own launches of
+ * several steps (lbm_step) are faster still keeps those.
  * The launches are consecutive steps, as stepping runs them (a launch repeated on one
  * unchanged buffer can be served from the GPU's last-level cache, 256 MB on
  * MI355X, where two buffers would not fit): the state is saved to a

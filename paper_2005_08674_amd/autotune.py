@@ -3,7 +3,8 @@
 The library times every compiled launch shape on a live lattice (median of
 repeated launches): ``lbm_autotune`` the single-step launch (the fused edge +
 bulk kernel), ``lbm_autotune_two_step`` the multi-step sweeps (two or three
-steps per launch) where the lattice supports them.  The fastest per step wins.  This module keeps the winners in
+steps per launch) where the lattice supports them, ``lbm_time_auto_launch`` the launches the library picks by
+itself where they are neither.  The fastest per step wins.  This module keeps the winners in
 ``tuning/tiles.json`` keyed by (GPU architecture, lattice size, storage), so
 later runs reuse a measured choice instead of re-timing, and records every
 candidate's time.
@@ -18,6 +19,8 @@ import os
 import time
 
 from . import lbm as L
+
+AUTO = "auto"  # multi-step entry of a lattice left to the library's own choice
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning", "tiles.json")
 
@@ -39,14 +42,14 @@ def load_cache(path: str = CACHE) -> dict:
 
 
 def lookup(nx: int, ny: int, store: str, path: str = CACHE, gpu_arch: str | None = None):
-    """Cached (tile name, two-step shape name or None) for this lattice, or None."""
+    """Cached (tile name, two-step shape name, AUTO or None) for this lattice, or None."""
     entry = load_cache(path).get(key(nx, ny, store, gpu_arch))
     if not entry:
         return None
     names = [L.lbm_tile_describe(i) for i in range(L.lbm_tile_count())]
     twos = [L.lbm_two_step_describe(i) for i in range(L.lbm_two_step_count())]
     two = entry.get("two_step")
-    if entry["tile"] not in names or (two is not None and two not in twos):
+    if entry["tile"] not in names or (two not in (None, AUTO) and two not in twos):
         return None
     return entry["tile"], two
 
@@ -59,7 +62,9 @@ def apply(lattice, store: str, path: str = CACHE) -> str | None:
     tile, two = hit
     names = [L.lbm_tile_describe(i) for i in range(L.lbm_tile_count())]
     L.lbm_set_tile(lattice.ctx, names.index(tile))
-    if two is not None:
+    if two == AUTO:
+        L.lbm_set_auto_launch(lattice.ctx)
+    elif two is not None:
         twos = [L.lbm_two_step_describe(i) for i in range(L.lbm_two_step_count())]
         L.lbm_set_two_step(lattice.ctx, twos.index(two))
     else:
@@ -68,9 +73,10 @@ def apply(lattice, store: str, path: str = CACHE) -> str | None:
 
 
 def tune(lattice, store: str, reps: int = 10, path: str | None = CACHE) -> dict:
-    """Time every candidate on ``lattice``: single-step tiles, then the multi-step shapes (two and three
-    steps per launch) if the lattice supports them; keep the fastest per step, select it, and record it
-    in the cache."""
+    """Time every candidate on ``lattice``: the library's own choice, single-step tiles, and the multi-step
+    shapes (two and three steps per launch) if the lattice supports them; keep the fastest per step, select
+    it, and record it in the cache."""
+    own = L.lbm_time_auto_launch(lattice.ctx, reps)
     best, times = L.lbm_autotune(lattice.ctx, reps)
     names = [L.lbm_tile_describe(i) for i in range(L.lbm_tile_count())]
     entry = {"tile": names[best], "ms": times[best], "reps": reps,
@@ -88,6 +94,11 @@ def tune(lattice, store: str, reps: int = 10, path: str | None = CACHE) -> dict:
             entry["two_step_ms"] = t2[b2]
         else:
             L.lbm_set_two_step(lattice.ctx, -1)
+    if own > 0:
+        entry["auto_ms"] = round(own, 5)
+        if own < min(times[best], entry.get("two_step_ms", times[best])):
+            entry["two_step"], entry["two_step_ms"] = AUTO, own
+            L.lbm_set_auto_launch(lattice.ctx)
     if path:
         cache = load_cache(path)
         cache[key(lattice.nx, lattice.ny, store)] = entry

@@ -973,7 +973,60 @@ struct StateSnapshot {
   }
 };
 
+// ms per step of the deep launches that lbm_step would choose for a lattice
+// nobody has chosen a launch for, over runs of kTuneRunSteps (median of `reps`
+// after a warm-up; state and t left unchanged); -1 where it would choose single
+// steps or a multi-step shape.
+int time_own_choice(lbm_ctx* c, int32_t reps, float* ms) {
+  *ms = -1.f;
+  if (c->timing || !use_fused(c) || capturing(c) || free_multi(c, kTuneRunSteps) >= 0) return LBM_OK;
+  const int id = deep_shape(c);
+  if (id < 0 || deep_min_steps(c) == 0) return LBM_OK;
+  StateSnapshot snap;
+  if (int rc = snap.save(c)) return rc;
+  const int parity = c->parity;
+  const int64_t t = c->t;
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  int rc = LBM_OK;
+  std::vector<float> ts(reps);
+  for (auto& e : ev)
+    if (rc == LBM_OK && hipEventCreate(&e) != hipSuccess) rc = fail(LBM_ERR_HIP, "event creation failed");
+  for (int r = -1; r < reps && rc == LBM_OK; ++r) {
+    hipError_t e = hipEventRecord(ev[0], c->stream);
+    int done = 0;
+    if (e == hipSuccess) rc = step_deep(c, id, kTuneRunSteps, &done);
+    for (; done < kTuneRunSteps && rc == LBM_OK; ++done) rc = step_once(c);
+    if (e == hipSuccess) e = hipEventRecord(ev[1], c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess && r >= 0) e = hipEventElapsedTime(&ts[r], ev[0], ev[1]);
+    if (e != hipSuccess && rc == LBM_OK) rc = fail(LBM_ERR_HIP, "timing the chosen launches: %s", hipGetErrorString(e));
+  }
+  for (auto& e : ev)
+    if (e) (void)hipEventDestroy(e);
+  c->parity = parity;
+  c->t = t;
+  const int back = snap.restore();
+  if (rc || back) return rc ? rc : back;
+  std::sort(ts.begin(), ts.end());
+  *ms = ts[reps / 2] / (float)kTuneRunSteps;
+  return LBM_OK;
+}
+
 }  // namespace
+
+int lbm_set_auto_launch(lbm_ctx* c) {
+  if (!c) return fail(LBM_ERR_ARG, "ctx is NULL");
+  c->two_step = -1;
+  c->chosen = false;
+  return LBM_OK;
+}
+
+int lbm_time_auto_launch(lbm_ctx* c, int32_t reps, float* ms) {
+  const lbm::TraceRange trace_range("lbm_time_auto_launch");
+  if (!c || !ms) return fail(LBM_ERR_ARG, "NULL argument");
+  if (reps < 1 || reps > 1000) return fail(LBM_ERR_ARG, "reps = %d outside [1, 1000]", reps);
+  return time_own_choice(c, reps, ms);
+}
 
 int lbm_autotune(lbm_ctx* c, int32_t reps, int32_t* best, float* times_ms) {
   const lbm::TraceRange trace_range("lbm_autotune");
@@ -1026,8 +1079,13 @@ int lbm_autotune(lbm_ctx* c, int32_t reps, int32_t* best, float* times_ms) {
   if (rc) return rc;
   if (int r = snap.restore()) return r;
   c->tile = best_id;
-  c->chosen = true;
   *best = best_id;
+  if (!c->chosen) {
+    // a lattice that is faster on the launches it has by itself keeps them
+    float own = -1.f;
+    if (int r = time_own_choice(c, reps, &own)) return r;
+    c->chosen = !(own >= 0.f && own < best_t);
+  }
   return LBM_OK;
 }
 

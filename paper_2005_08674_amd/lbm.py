@@ -86,6 +86,8 @@ _SIGS = {
     "lbm_two_step_count": [],
     "lbm_two_step_describe": [ctypes.c_int32, _P, ctypes.c_size_t],
     "lbm_two_step_steps": [ctypes.c_int32, _P],
+    "lbm_set_auto_launch": [_P],
+    "lbm_time_auto_launch": [_P, ctypes.c_int32, _P],
     "lbm_set_two_step": [_P, ctypes.c_int32],
     "lbm_get_two_step": [_P, _P],
     "lbm_autotune_two_step": [_P, ctypes.c_int32, _P, _P],
@@ -357,6 +359,18 @@ def lbm_two_step_steps(shape_id: int) -> int:
     k = ctypes.c_int32()
     _check(load().lbm_two_step_steps(int(shape_id), ctypes.byref(k)), "lbm_two_step_steps")
     return k.value
+
+
+def lbm_set_auto_launch(ctx):
+    """Leave the launches of lbm_step to the library again."""
+    _check(load().lbm_set_auto_launch(ctx), "lbm_set_auto_launch")
+
+
+def lbm_time_auto_launch(ctx, reps: int = 5) -> float:
+    """ms per step of the launches the library picks by itself; -1 where the tuners time them anyway."""
+    ms = ctypes.c_float()
+    _check(load().lbm_time_auto_launch(ctx, int(reps), ctypes.byref(ms)), "lbm_time_auto_launch")
+    return ms.value
 
 
 def lbm_set_two_step(ctx, shape_id: int):
