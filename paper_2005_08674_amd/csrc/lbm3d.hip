@@ -709,7 +709,10 @@ static bool shape3_supported(const Lat3& L, int id) {
 // blocks, 31 / 141 / 460 with whole rows; BF16 36 / 167 / 459 with 64 x 4 and 31 / 133 /
 // 396 with 64 x 2 one-node blocks, - / 96 / 247 and - / 90 / 249 with pairs in 64 x 2
 // and 128 x 1 blocks (64 wide, D3Q27 FP16: 17.9 one-node 64 x 2, 18.8 pairs).  The wider
-// block is taken where it leaves no more lanes idle.
+// block is taken where it leaves no more lanes idle: with 64 x 4, 128 x 1 and 256 x 1 blocks
+// D3Q19 FP64 takes 126 / 122 / 124 at 128^3 (128 / 123 / 123 with periodic faces), 70 / 68 / 68
+// at 100^3, 111 / 118 / 113 at 192 x 100 x 100, 146 / 143 / 151 at 384 x 100 x 64, 126 / 122 / 119
+// at 256 x 128 x 64 periodic; FP32 follows (65 / 63 / 65 at 128^3).
 static int default_shape3(const Lat3& L) {
   auto find = [](auto& list, int bx, int by, int zc) {
     int i = 0;
@@ -721,7 +724,8 @@ static int default_shape3(const Lat3& L) {
     const int pair = kNumShapes3 + (wide(L.nx / 2, 128) ? find(kPairs3, 128, 1, 1) : find(kPairs3, 64, 2, 1));
     return L.nx > 64 && shape3_supported(L, pair) ? pair : find(kShapes3, 64, 2, 1);
   }
-  return wide(L.nx, 256) ? kFirstRow3 : find(kShapes3, 64, 4, 1);
+  if (wide(L.nx, 256)) return kFirstRow3;
+  return wide(L.nx, 128) ? find(kShapes3, 128, 1, 1) : find(kShapes3, 64, 4, 1);
 }
 
 template <int S, int NQ, int BX, int BY, int ZC, bool NTL>
