@@ -382,10 +382,11 @@ int build_tiles(lbm_ens* e, int shape) {
 // Multi-step shapes: ids below num_two_step() are two-step shapes, the next
 // num_three_step() three-step shapes (as in the single-lattice API).
 constexpr size_t kListRun = 8, kL2Bytes = (size_t)32 << 20;
-// Tiles from which an ensemble's three-step sweep marches its larger members: two per block that the GPU holds
-// at once.  A march item runs about four times as long as a tile, which below that leaves CUs idle (us per
+// Tiles from which an ensemble's three-step sweep marches its larger members, as measured: a march item runs
+// about four times as long as a tile, which with few of them leaves CUs idle (us per
 // pass in tiles and marched, at tiles of 12 rows: FP64 36 members, 692 tiles 1030 and 1160; FP64 44 members, 1073 tiles
-// 685 and 622; FP16 13 members, 1143 tiles 667 and 548; FP32 14 members, 1203 tiles 420 and 367).
+// 685 and 622; FP16 13 members, 1143 tiles 667 and 548; FP32 14 members, 1203 tiles 420 and 367).  The GPU holds
+// 256 blocks of the FP64 shapes at once, 512 or 768 of the others; one limit serves them all.
 constexpr size_t kMarchTiles = 1024;
 int ens_multi_count() { return lbm::num_two_step() + lbm::num_three_step(); }
 int ens_multi_steps(int id) { return id < lbm::num_two_step() ? 2 : 3; }
