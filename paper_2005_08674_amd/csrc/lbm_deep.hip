@@ -48,7 +48,7 @@ constexpr int deep_waves() {
   return S == ST_F64 ? 1 : (NT == 1024 ? 8 : (NT == 704 ? 6 : 1));
 }
 
-template <int S, int CM, bool UB0, int TX, int TY, int KM, bool NTS>
+template <int S, int CM, bool UB0, int TX, int TY, int KM>
 __global__ __launch_bounds__((DeepShape<TX, TY, KM>::NT), (deep_waves<S, DeepShape<TX, TY, KM>::NT>())) void k_deep(LatDesc L, int parity, int tiles_x, int ntiles,
                                                                      int k) {
   using D = DeepShape<TX, TY, KM>;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__((DeepShape<TX, TY, KM>::NT), (deep_waves<S, DeepSha
       for (int i = 0; i < 9; ++i) node[i * N] = v[i];
     } else if (stores) {
 #pragma unroll
-      for (int i = 0; i < 9; ++i) out.template put<NTS>(i, own, v[i]);
+      for (int i = 0; i < 9; ++i) out.template put<false>(i, own, v[i]);
     }
   };
   // Both kinds of wavefront pass the same barriers: one after a level's writes
@@ -174,7 +174,13 @@ __global__ __launch_bounds__((DeepShape<TX, TY, KM>::NT), (deep_waves<S, DeepSha
   const uint32_t unknown = tl_unknown(xper ? 1 : x, yper ? 1 : y, xper ? 3 : nx, yper ? 3 : ny);
   // A level's update from `pull(px, py, i)`, population i of the node (px, py)
   // away (within one of it; an unknown one is read at the nearest node of the
-  // lattice and dropped), and `mom(px, py, m)`, the moments of such a node.
+  // lattice and dropped), and `mom(px, py, m)`, the moments of the node itself or
+  // of one up to two nodes inward of an NSBC edge.  Those lie in the region and are
+  // there at the level before: an NSBC edge crosses a region only as an outermost
+  // row or column of the tile (tiles are whole and a margin narrower than a tile,
+  // deep_supported), so two nodes inward is a row or column of the tile, no nearer
+  // to the region's border than the node.
+  static_assert(TX >= 3 && TY >= 3, "NSBC reads two nodes inward");
   const int xm = x == 0 && !xper ? 0 : -1, xp = x == nx - 1 && !xper ? 0 : 1;
   const int ym = y == 0 && !yper ? 0 : -1, yp = y == ny - 1 && !yper ? 0 : 1;
   M3<R> mc = {{R(0), R(0), R(0)}};
@@ -262,7 +268,7 @@ static hipError_t launch_deep_t(const LatDesc& L, int parity, int k, hipStream_t
   const int tx = (L.nx + TX - 1) / TX, n = tx * ((L.ny + TY - 1) / TY);
   const dim3 grid((n + 7) / 8 * 8), block(DeepShape<TX, TY, KM>::NT);
   auto launch = [&](auto cm, auto ub0) {
-    k_deep<S, decltype(cm)::value, decltype(ub0)::value, TX, TY, KM, false><<<grid, block, 0, s>>>(L, parity, tx, n, k);
+    k_deep<S, decltype(cm)::value, decltype(ub0)::value, TX, TY, KM><<<grid, block, 0, s>>>(L, parity, tx, n, k);
   };
   const std::integral_constant<int, COLL_MRT> mrt;
   const std::integral_constant<int, COLL_BGK> bgk;
