@@ -142,9 +142,9 @@ int lbm_set_velocity_edge(lbm_ctx* ctx, double ux, double uy);
  * lbe_1).  Asynchronous; the context's time advances by n.  Until a launch
  * shape is chosen (lbm_set_tile, lbm_autotune, lbm_set_two_step or
  * lbm_autotune_two_step) and while fusion is on, overlap, per-kernel timing
- * and the closure off, the library picks the launches of n >= 2 steps by the
- * lattice's size, edges and storage: several steps per launch, with the
- * results of single steps, bit for bit.  A call recorded into a HIP graph
+ * and the closure off, the library picks the launches of n >= 2 steps by n and the
+ * lattice's size, edges, storage, collision model and base velocity: several steps
+ * per launch where that is faster, with the results of single steps, bit for bit.  A call recorded into a HIP graph
  * keeps to one launch per step, so that a graph of an even number of steps
  * can be replayed to go on stepping.  The call is a
  * roctx range named "lbm_step" (as are the other stepping and tuning calls,
@@ -328,9 +328,11 @@ int lbm_set_fused(lbm_ctx* ctx, int on);
  * population per node, plus margins re-read from L2), and results are
  * bit-identical to single steps: intermediate levels are held in the
  * storage format exactly as a store would write them.  Column-march shapes
- * ("...+march<MR>xh<H>..."): one launch runs the edge tiles (the ring of
- * 64 x TY tiles around the inner tiles' rectangle) as tiles and the inner
- * rectangle as 64-column strips cut into chunks of about H rows, each
+ * ("...+march<MR>xh<H>..."): one launch runs the edge tiles (64 x TY
+ * along the bottom and the top, and along the sides 64 x TY in the two-step
+ * shapes, 16 x 4 TY in the three-step ones) as tiles and the
+ * rest as 64-column strips cut into chunks of about H rows (the three-step ones
+ * shorter where the lattice has few of them), each
  * walked down in rounds of MR rows with every intermediate level's last
  * MR + 2 rows in an LDS ring, so no row margin is recomputed; same
  * conditions and results as the tile shapes of that TY.  They are single-
@@ -349,7 +351,7 @@ int lbm_set_fused(lbm_ctx* ctx, int on);
  * single-step edge kernel does (bit-identical to closure single steps; the
  * edge tiles then run in a kernel of their own on a second stream beside
  * the inner tiles or strips; each launch's edge-tile kernel waits only for
- * the previous launch's inner part, and before lbm_step returns the stream
+ * the border of the previous launch's inner part, and before lbm_step returns the stream
  * has waited for the last of them); two-step shapes and remainders then run
  * as closure single steps.  The
  * overlap option and periodic edges always use the single-step kernels.

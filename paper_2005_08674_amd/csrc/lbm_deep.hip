@@ -1,6 +1,7 @@
 // lbm_deep.hip -- several time steps per launch for a lattice with any edges
 // (NSBC, periodic, velocity inlet): what lbm_step runs when no launch has been
-// chosen for the lattice.
+// chosen for the lattice, as far as it is faster there than single steps and the
+// 64-wide sweeps.
 //
 // A block owns a TX x TY output tile and computes it k <= KM steps ahead.  Its
 // region is the tile widened by KM - 1 nodes on every side, one node per

@@ -37,9 +37,10 @@ constexpr int two_step_waves() {
 
 // ------------------------------------------------------------------ column march
 // Candidate shapes of the marched three-step sweep, one launch of NT-thread
-// blocks: the edge tiles (the ring around the inner tiles' rectangle) as
-// three-step tiles of 64 x TY, then the rectangle as 64-column strips cut
-// into chunks of about H rows, each walked down in rounds of MR rows
+// blocks: the edge tiles (MarchGeom: 64 x TY along the bottom and the top, 16 x 4 TY
+// along the sides), then the rest as 64-column strips cut
+// into chunks of about H rows (shorter on a lattice of few blocks,
+// march_chunks_filled), each walked down in rounds of MR rows
 // (three_step_march) with PF rounds of loads in flight; the march's level
 // rings take the tiles' level arrays.  NT threads cover a round's MR x 68
 // level-(t + 1) nodes in one pass; NTS: non-temporal stores (plain stores

@@ -182,6 +182,7 @@ void three_step_name(int id, char* buf, size_t len) {
     snprintf(buf, len, "invalid");
     return;
   }
+  // (the names are identifiers that callers keep: a march's is "+xcdband" from when its XCDs took bands)
   const ThreeStepShape& t = kThree[id];
   if (t.mr > 0)
     snprintf(buf, len, "3step:64x%d/%d+march%dxh%d%s+xcdband%s", t.ty, t.nt, t.mr, t.h, t.pf == 2 ? "+pf2" : "",
@@ -219,9 +220,9 @@ static int tile_shape_of(int id) {
 // middle and need to end only before that launch's border is through (with kJoinDefer
 // on every launch but the last and kJoinPrev on every launch but the first).  With the
 // middle first, the edge tiles started after it and the next border waited for them.
-// 2048^2 FP32 on the vortex, most side tiles through the regime gate: 128 -> 103 us per
-// launch together with the narrower edge tiles and the weights in registers (one
-// fork and join per launch, border and middle in one kernel: 109 to 121).
+// 2048^2 FP32 on the vortex, us per launch with the middle first and 64-wide edge tiles /
+// as it is: most side nodes past the regime gate 117 / 96, few of them 93 / 92 (one
+// fork and join per launch, border and middle in one kernel: 109 to 121 past the gate).
 hipError_t launch_three_step(const LatDesc& L, int parity, int id, hipStream_t s, hipStream_t side, hipEvent_t fork,
                              hipEvent_t join, int flags) {
   if (!three_step_supported(L, id)) return hipErrorInvalidValue;

@@ -746,8 +746,9 @@ __device__ __attribute__((always_inline)) inline void three_step_tile_at(const L
     return mc;
   };
   // the network's parameters in LDS (CL; read after the first closure phase's barrier)
-  // and its weights in registers: read per level and layer they came through an L2 that the march
-  // beside this kernel streams through (2048^2: a level of a side tile past the gate 12.5 -> 8.4 us)
+  // and its weights in registers, once a node of the wave's passes the gate: read per level and layer they came
+  // through an L2 that the march beside this kernel streams through (2048^2: a level of a side tile past the
+  // gate 12.5 -> 8.4 us)
   mlp::Params par{};
   mlp::Frags weights;
   bool have = false;
