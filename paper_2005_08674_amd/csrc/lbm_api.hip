@@ -606,11 +606,15 @@ int deep_shape(const lbm_ctx* c) {
 //   12.3 / 10.8 against 16.8, 2048^2 59 / 47 / 39 against 56, and in 768 to 1024 tiles
 //   of 16 x 16, short of two rounds, 3000 x 80 8.9 / 6.2 / 5.4 against 8.8;
 //   FP16 701^2 8.3 / 6.5 / 5.5 against 9.5, 1000 x 1024 13.4 / 10.4 / 9.2 against 12.4,
-//   3001 x 2047 60 / 47 / 39 against 46, 4096^2 160 / 129 / 108 against 108;
+//   3001 x 2047 60 / 47 / 39 against 46, 4096^2 160 / 129 / 104 against 112, 8192^2
+//   - / - / 406 against 484;
 //   FP16 MRT 512^2 6.9 / 5.9 / 5.4 against 8.4, 701^2 10.0 / 8.0 / 7.0 against 9.7,
 //   1000 x 1024 16.5 / 13.2 / 12.2 against 12.5, 2048 x 1024 28 / 23 / 21 against 20;
 //   FP16 with a base velocity 3000 x 80 8.0 / 5.8 / 5.1 against 7.8 (on four NSBC edges
-//   10.0 / 7.0 / 6.1), 1000 x 1024 16.7 / 13.2 / 11.5 against 12.6.
+//   10.0 / 7.0 / 6.1), 1000 x 1024 16.7 / 13.2 / 11.5 against 12.6, and with 4 steps 2048 x 1024
+//   19.3 against 18.7, 1700 x 1600 22.7 / 24.0, 1900^2 29.3 / 32.4, 2048^2 33.4 / 36.4, 2200^2 37.5 /
+//   37.9, 2560^2 51.2 / 50.0 (BF16 59.4 / 50.6), 4096^2 121 / 115; MRT 1900^2 32.9 / 34.3, 2000 x 1700
+//   30.5 / 29.3, 2560^2 57.4 / 53.5.
 int deep_min_steps(const lbm_ctx* c) {
   const int64_t nodes = nodes_of(c), k = 1 << 16;
   if (c->p.store == LBM_STORE_F64) return c->L.ub_zero || std::min(c->p.nx, c->p.ny) >= 128 ? 2 : 3;
@@ -618,9 +622,10 @@ int deep_min_steps(const lbm_ctx* c) {
     return c->L.ub_zero || nodes <= 3 * k || (nodes > 4 * k && nodes < 64 * k) ? 2 : 3;
   if (is_heavy(c)) {
     if (nodes <= (c->L.ub_zero ? 4 : 3) * k) return 2;
-    return nodes < 8 * k ? 3 : (nodes < 24 * k ? 4 : 0);
+    if (nodes < 24 * k) return nodes < 8 * k ? 3 : 4;
+    return c->L.coll != lbm::COLL_MRT && nodes >= 40 * k && nodes <= 66 * k ? 4 : 0;
   }
-  return nodes < 8 * k ? 2 : (nodes < 80 * k ? 3 : (nodes < 128 * k ? 4 : 0));
+  return nodes < 8 * k ? 2 : (nodes < 80 * k ? 3 : 4);
 }
 
 // Up to n steps in deep launches, *done of them: as few launches as they take

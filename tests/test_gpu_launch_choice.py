@@ -28,7 +28,9 @@ CHANNEL, BOX, PERIODIC = (1, 1, 0, 0), (1, 1, 1, 1), (0, 0, 0, 0)
     (2048, 1024, "bf16", CHANNEL, dict(u=0.05), 4, False), (3000, 80, "f16", BOX, dict(u=0.05), 2, False),
     (3000, 80, "f16", BOX, dict(u=0.05), 3, True), (2200, 2100, "f32", CHANNEL, dict(u=0.05), 2, False),
     (2200, 2100, "f32", CHANNEL, dict(u=0.05), 3, True), (3001, 2047, "f16", CHANNEL, {}, 3, False),
-    (4096, 2200, "f16", PERIODIC, {}, 4, False), (2048, 1024, "f16", BOX, dict(mrt=True), 2, False),
+    (4096, 2200, "f16", PERIODIC, {}, 3, False), (4096, 2200, "f16", PERIODIC, {}, 4, True),
+    (1900, 1900, "bf16", PERIODIC, dict(u=0.05), 4, True), (2560, 2560, "f16", PERIODIC, dict(u=0.05), 4, False),
+    (2048, 1024, "f16", BOX, dict(mrt=True), 2, False),
     (1000, 1024, "f16", BOX, dict(mrt=True), 3, True)])
 def test_one_launch_only_where_it_is_faster(nx, ny, store, bc, kw, n, one):
     """One launch leaves the buffer it read as it was; more than one write to it."""
